@@ -54,9 +54,7 @@ void release(Plan *p) {
     if (p->ev_fork) (void)hipEventDestroy(p->ev_fork);
     if (p->cap_stream) (void)hipStreamDestroy(p->cap_stream);
     (void)hipFree(p->d_queue);
-    (void)hipFree(p->d_var_off);
-    (void)hipFree(p->d_clause_off);
-    (void)hipFree(p->d_feat_acc);
+    (void)hipFree(p->d_tile);
     (void)hipFree(p->d_fd);
     (void)hipFree(p->d_work);
     (void)hipFree(p->d_work_fb);
@@ -695,10 +693,11 @@ hp_status hp_plan(hp_plan_t *out, const hp_cnf *cnf, const hp_rbm *rbm, const hp
     HP_TRY(upload(&p->d_orig, orig, s), "upload clause order");
     HP_TRY(upload(&p->d_negcnt, negcnt, s), "upload negation counts");
     HP_TRY(upload(&p->d_temp, temp, s), "upload temperatures");
-    std::vector<int64_t> voff(cnf->var_offset, cnf->var_offset + F + 1);
-    std::vector<int64_t> coff(cnf->clause_offset, cnf->clause_offset + F + 1);
-    HP_TRY(upload(&p->d_var_off, voff, s), "upload variable offsets");
-    HP_TRY(upload(&p->d_clause_off, coff, s), "upload clause offsets");
+    std::vector<VarTile> tiles;
+    for (int f = 0; f < F; ++f)
+        for (int32_t i = 0; i < fd[f].n; i += kTileVars) tiles.push_back({f, i});
+    p->n_tiles = (int32_t)tiles.size();
+    HP_TRY(upload(&p->d_tile, tiles, s), "upload variable tiles");
     HP_TRY(upload(&p->d_W, Wv, s), "upload W_c");
     HP_TRY(upload(&p->d_b, bv, s), "upload b_c");
     if (clust) {
@@ -974,11 +973,7 @@ hp_status hp_features(hp_plan_t plan, uint16_t *x, void *stream) {
     Plan *p = reinterpret_cast<Plan *>(plan);
     if (!p || !x) return fail(HP_EINVAL, "null argument");
     if (p->K > 7 || p->total_vars < 1) return fail(HP_EINVAL, "bad plan");
-    if (!p->d_feat_acc) {
-        hipError_t e = hipMalloc((void **)&p->d_feat_acc, (size_t)p->total_vars * 20 * sizeof(float));
-        if (e != hipSuccess) return hip_fail(e, "feature workspace");
-    }
-    hipError_t e = launch_features(*p, p->d_feat_acc, x, (hipStream_t)stream);
+    hipError_t e = launch_features(*p, x, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "feature kernels");
     return HP_OK;
 }

@@ -35,6 +35,14 @@ struct WorkItem {
     int32_t b;            // chain within the formula
 };
 
+// Variables [i0, min(i0 + kTileVars, N_f)) of formula f: the unit of work of
+// the kernels that go over the variables of a whole batch.
+constexpr int kTileVars = 1024;
+struct VarTile {
+    int32_t f;
+    int32_t i0;
+};
+
 // Device tables prepared once per plan (per temperature tau):
 //   thr[tau][m][l] = ceil(2^24 * sigma(b_c[l] + sum_k W_c[k,l] * bit_k(m)))
 //       so that the hidden draw (word >> 8) < thr  <=>  U < p(h_l = 1 | m)
@@ -238,9 +246,8 @@ struct Plan {
     hipStream_t cap_stream = nullptr;
     std::vector<GraphEntry> graphs;
     uint32_t *d_queue = nullptr;     // [kMaxBuckets][kQueueWords] persistent work counters
-    int64_t *d_var_off = nullptr;    // [F+1]
-    int64_t *d_clause_off = nullptr; // [F+1]
-    float *d_feat_acc = nullptr;     // feature workspace, allocated on first use
+    VarTile *d_tile = nullptr;       // [n_tiles] variable tiles of all formulas, in order
+    int32_t n_tiles = 0;
     // device memory
     FormulaDev *d_fd = nullptr;
     WorkItem *d_work = nullptr;
@@ -320,7 +327,7 @@ size_t lds_bytes_push(int max_n, int kind, int32_t *v_off, int32_t *x_off);
 size_t lds_bytes_clust(int max_n, int32_t *v_off, int32_t *x_off);
 
 // learned initial assignments (hp_mlp.hip)
-hipError_t launch_features(const Plan &p, float *acc, uint16_t *x, hipStream_t s);
+hipError_t launch_features(const Plan &p, uint16_t *x, hipStream_t s);
 hipError_t launch_mlp(const hp_mlp &net, const uint16_t *x, const float *y, int64_t rows, float *q,
                       float *loss_sum, bool backward, hipStream_t s);
 hipError_t launch_adam(const hp_mlp &net, float lr, float beta1, float beta2, float eps, int64_t step,

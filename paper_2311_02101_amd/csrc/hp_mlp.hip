@@ -23,7 +23,6 @@ namespace hp {
 constexpr int kF = HP_MLP_IN;
 constexpr int kH = HP_MLP_HIDDEN;
 constexpr int kOffW1 = 0, kOffB1 = kF * kH, kOffW2 = kOffB1 + kH, kOffB2 = kOffW2 + kH;
-constexpr int kFeatAcc = 20;   // accumulated raw features per variable
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
@@ -36,50 +35,92 @@ __device__ __forceinline__ float bf16_value(uint16_t u) {
     return __builtin_bit_cast(float, (uint32_t)u << 16);
 }
 
-// formula of a global index, by binary search over prefix offsets [F+1]
-__device__ __forceinline__ int formula_of(const int64_t *off, int F, int64_t g) {
-    int lo = 0, hi = F;   // off[lo] <= g < off[hi]
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (off[mid] <= g) lo = mid;
-        else hi = mid;
-    }
-    return lo;
-}
-
 // ---- features ----------------------------------------------------------------
-__global__ void feature_count_kernel(const uint4 *__restrict__ rec, const int64_t *__restrict__ clause_off,
-                                     const FormulaDev *__restrict__ fd, int F, int64_t ctot,
-                                     float *__restrict__ acc) {
-    for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < ctot; c += (int64_t)gridDim.x * blockDim.x) {
-        const int f = formula_of(clause_off, F, c);
-        const int64_t v0 = fd[f].var_off;
-        const uint4 r = rec[c];
-        const uint32_t e[7] = {r.x & 0xffffu, r.x >> 16, r.y & 0xffffu, r.y >> 16, r.z & 0xffffu, r.z >> 16,
-                               r.w & 0xffffu};
-        const int len = (int)rec_len(r.w);
-        const float jw = ldexpf(1.0f, -len);
-        for (int k = 0; k < len; ++k) {
-            const int64_t v = v0 + (e[k] & 0x7fffu);
-            const int neg = (int)(e[k] >> 15);
-            atomicAdd(&acc[v * kFeatAcc + 2 * (len - 1) + neg], 1.0f);
-            atomicAdd(&acc[v * kFeatAcc + 14 + neg], 1.0f);
-            atomicAdd(&acc[v * kFeatAcc + 17 + neg], jw);
-        }
-    }
-}
+// One workgroup per tile of 1024 variables: it scans the formula's clause
+// records and counts, in LDS, the 14 (length, sign) occurrences of its
+// variables; every other feature is a sum of those counts.  Bound by the LDS
+// counter updates and the scan (16 bytes a clause and tile, from L2 after the
+// formula's first tile).  Counting in LDS, one update per literal, takes the
+// place of three FP32 global atomics per literal, which ran at about 20 G
+// atomics/s: FEATURE_NUMBERS.
+// 57 KB of counters let two workgroups of 1024 threads share a CU.
+constexpr int kFeatThreads = 1024;
+constexpr int kFeatBins = 14;
 
-__global__ void feature_finish_kernel(const float *__restrict__ acc, int64_t nv, uint16_t *__restrict__ x) {
-    for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < nv; v += (int64_t)gridDim.x * blockDim.x) {
-        const float *a = acc + v * kFeatAcc;
-        float f[kF];
-        for (int j = 0; j < 16; ++j) f[j] = a[j] * 0.125f;
-        f[16] = (a[14] - a[15]) * 0.125f;
-        f[17] = a[17];
-        f[18] = a[18];
-        f[19] = a[17] - a[18];
-        for (int j = 20; j < kF; ++j) f[j] = 0.0f;
-        for (int j = 0; j < kF; ++j) x[v * kF + j] = bf16_bits(f[j]);
+__global__ __launch_bounds__(kFeatThreads) void feature_kernel(const uint4 *__restrict__ rec,
+                                                               const FormulaDev *__restrict__ fd,
+                                                               const VarTile *__restrict__ tile,
+                                                               uint16_t *__restrict__ x, bool vec) {
+    __shared__ uint32_t s_cnt[kFeatBins][kTileVars];
+    const VarTile t = tile[blockIdx.x];
+    const FormulaDev &f = fd[t.f];
+    const uint4 *__restrict__ r = rec + f.clause_off;
+    const int C = f.c, nv = min(kTileVars, f.n - t.i0), tid = threadIdx.x;
+    for (int i = tid; i < kFeatBins * kTileVars; i += kFeatThreads) (&s_cnt[0][0])[i] = 0u;
+    __syncthreads();
+    auto count = [&](const uint4 &q) {
+        const uint32_t e[7] = {q.x & 0xffffu, q.x >> 16, q.y & 0xffffu, q.y >> 16, q.z & 0xffffu, q.z >> 16,
+                               q.w & 0xffffu};
+        const int len = (int)rec_len(q.w);
+#pragma unroll
+        for (int k = 0; k < kMaxK; ++k) {
+            if (k < len) {
+                const uint32_t i = (e[k] & 0x7fffu) - (uint32_t)t.i0;
+                if (i < (uint32_t)nv) atomicAdd(&s_cnt[2 * (len - 1) + (int)(e[k] >> 15)][i], 1u);
+            }
+        }
+    };
+    // two records in flight per thread
+    int c = tid;
+    for (; c + kFeatThreads < C; c += 2 * kFeatThreads) {
+        const uint4 q0 = r[c], q1 = r[c + kFeatThreads];
+        count(q0);
+        count(q1);
+    }
+    if (c < C) count(r[c]);
+    __syncthreads();
+    // four threads write the 64-byte row of a variable, 16 bytes (8 features) each
+    uint16_t *__restrict__ row = x + (size_t)(f.var_off + t.i0) * kF;
+    for (int j = tid; j < 4 * nv; j += kFeatThreads) {
+        const int i = j >> 2, part = j & 3;
+        float g[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+        if (part < 3) {
+            float cf[kFeatBins];
+            uint32_t occ[2] = {0u, 0u};
+            double w[2] = {0.0, 0.0};       // sums of 2^-length, exact
+#pragma unroll
+            for (int b = 0; b < kFeatBins; ++b) {
+                const uint32_t n = s_cnt[b][i];
+                cf[b] = (float)n * 0.125f;
+                occ[b & 1] += n;
+                w[b & 1] += (double)n * (1.0 / (double)(2 << (b >> 1)));
+            }
+            const float p = (float)occ[0], m = (float)occ[1], wp = (float)w[0], wm = (float)w[1];
+            if (part == 0) {
+#pragma unroll
+                for (int b = 0; b < 8; ++b) g[b] = cf[b];
+            } else if (part == 1) {
+#pragma unroll
+                for (int b = 8; b < kFeatBins; ++b) g[b - 8] = cf[b];
+                g[6] = p * 0.125f;
+                g[7] = m * 0.125f;
+            } else {
+                g[0] = (p - m) * 0.125f;
+                g[1] = wp;
+                g[2] = wm;
+                g[3] = wp - wm;
+            }
+        }
+        uint32_t o[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) o[b] = (uint32_t)bf16_bits(g[2 * b]) | ((uint32_t)bf16_bits(g[2 * b + 1]) << 16);
+        uint16_t *dst = row + (size_t)i * kF + part * 8;
+        if (vec) {
+            *reinterpret_cast<uint4 *>(dst) = make_uint4(o[0], o[1], o[2], o[3]);
+        } else {
+#pragma unroll
+            for (int b = 0; b < 8; ++b) dst[b] = (uint16_t)(o[b >> 1] >> (16 * (b & 1)));
+        }
     }
 }
 
@@ -378,39 +419,86 @@ __global__ void weights_to_bf16_kernel(const float *__restrict__ p, uint16_t *__
     }
 }
 
-__global__ void zero_f32_kernel(float *p, int64_t n) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = 0.0f;
+// Four consecutive bytes at any alignment (the rows of a state start wherever
+// the formula's size puts them), the first m of them if fewer are left.
+__device__ __forceinline__ uint32_t load_bytes4(const uint8_t *p, int m) {
+    uint32_t w = 0;
+    if (m >= 4) {
+        __builtin_memcpy(&w, p, 4);
+    } else {
+        for (int k = 0; k < m; ++k) w |= (uint32_t)p[k] << (8 * k);
+    }
+    return w;
+}
+__device__ __forceinline__ void store_bytes4(uint8_t *p, uint32_t w, int m) {
+    if (m >= 4) {
+        __builtin_memcpy(p, &w, 4);
+    } else {
+        for (int k = 0; k < m; ++k) p[k] = (uint8_t)(w >> (8 * k));
+    }
 }
 
 // ---- initial assignments v = [U < q] at the reserved time 2^64 - 1 -------------
-__global__ void init_chains_kernel(const float *__restrict__ q, const int64_t *__restrict__ var_off, int F,
-                                   int64_t nv, int B, int chain_lo, uint32_t key0, uint32_t key1,
-                                   uint8_t *__restrict__ v) {
-    const int b = chain_lo + blockIdx.y;
-    for (int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; g < nv; g += (int64_t)gridDim.x * blockDim.x) {
-        const int f = formula_of(var_off, F, g);
-        const int64_t i = g - var_off[f];
-        const int64_t n = var_off[f + 1] - var_off[f];
-        const uint4 r = philox4x32_10_lane_key(
-            make_uint4(0xffffffffu, (uint32_t)b, kPhaseVisible | (uint32_t)(i >> 2), 0xffffffffu),
-            Key2{key0, key1 ^ (uint32_t)f});
-        const uint32_t w = (i & 3) == 0 ? r.x : (i & 3) == 1 ? r.y : (i & 3) == 2 ? r.z : r.w;
-        const float u = (float)(w >> 8) * (1.0f / 16777216.0f);
-        v[var_off[f] * B + (int64_t)b * n + i] = u < q[g] ? 1 : 0;
+// A thread owns one group of four variables (the words of one Philox block)
+// of a tile and walks over the chains: the block is evaluated once for its
+// four variables, q stays in registers and a chain's four bytes are one
+// store.  Bound by the generator (about 60 lane instructions per four variables
+// and chain): 32 chains of 256 formulas of 2048 variables take 12.9 us, before
+// 88 us with a block, a search for the formula and a byte store per variable.
+constexpr int kTileGroups = kTileVars / 4;
+
+__global__ __launch_bounds__(kTileGroups) void init_chains_kernel(const float *__restrict__ q,
+                                                                  const FormulaDev *__restrict__ fd,
+                                                                  const VarTile *__restrict__ tile, int B, int lo,
+                                                                  int hi, uint32_t key0, uint32_t key1,
+                                                                  uint8_t *__restrict__ v) {
+    const VarTile t = tile[blockIdx.x];
+    const int n = fd[t.f].n;
+    const int64_t off = fd[t.f].var_off;
+    const int i = t.i0 + 4 * (int)threadIdx.x, m = n - i;
+    if (m <= 0) return;
+    float qv[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) qv[k] = k < m ? q[off + i + k] : 0.0f;
+    const Key2 key{key0, key1 ^ (uint32_t)t.f};
+    for (int b = lo + (int)blockIdx.y; b < hi; b += (int)gridDim.y) {
+        const uint4 r = philox4x32_10(make_uint4(0xffffffffu, (uint32_t)b, kPhaseVisible | (uint32_t)(i >> 2),
+                                                 0xffffffffu), key);
+        const uint32_t rw[4] = {r.x, r.y, r.z, r.w};
+        uint32_t w = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float u = (float)(rw[k] >> 8) * (1.0f / 16777216.0f);
+            w |= (u < qv[k] ? 1u : 0u) << (8 * k);
+        }
+        store_bytes4(v + off * B + (int64_t)b * n + i, w, m);
     }
 }
 
 // ---- per-variable mean over the chains of a state-layout byte array -------------
-__global__ void chain_mean_kernel(const uint8_t *__restrict__ a, const int64_t *__restrict__ var_off, int F,
-                                  int64_t nv, int B, float *__restrict__ out) {
-    for (int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; g < nv; g += (int64_t)gridDim.x * blockDim.x) {
-        const int f = formula_of(var_off, F, g);
-        const int64_t i = g - var_off[f], n = var_off[f + 1] - var_off[f];
-        int s = 0;
-        for (int b = 0; b < B; ++b) s += a[var_off[f] * B + (int64_t)b * n + i];
-        out[g] = (float)s / (float)B;
+// A thread sums four variables over the chains, one four-byte load per chain:
+// 5.3 us for 32 chains of 128 formulas of 2048 variables (8.4 MB), before 12.1 us
+// with a byte load per variable and a search for the formula.
+__global__ __launch_bounds__(kTileGroups) void chain_mean_kernel(const uint8_t *__restrict__ a,
+                                                                 const FormulaDev *__restrict__ fd,
+                                                                 const VarTile *__restrict__ tile, int B,
+                                                                 float *__restrict__ out) {
+    const VarTile t = tile[blockIdx.x];
+    const int n = fd[t.f].n;
+    const int64_t off = fd[t.f].var_off;
+    const int i = t.i0 + 4 * (int)threadIdx.x, m = n - i;
+    if (m <= 0) return;
+    const uint8_t *p = a + off * B + i;
+    int s[4] = {0, 0, 0, 0};
+#pragma unroll 8
+    for (int b = 0; b < B; ++b) {
+        const uint32_t w = load_bytes4(p + (int64_t)b * n, m);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) s[k] += (int)((w >> (8 * k)) & 0xffu);
     }
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (k < m) out[off + i + k] = (float)s[k] / (float)B;
 }
 
 // ---- launchers --------------------------------------------------------------
@@ -419,11 +507,9 @@ static int grid_for(int64_t n, int per_block, int cap) {
     return (int)std::max<int64_t>(1, std::min<int64_t>(g, cap));
 }
 
-hipError_t launch_features(const Plan &p, float *acc, uint16_t *x, hipStream_t s) {
-    zero_f32_kernel<<<grid_for(p.total_vars * kFeatAcc, 256, 4096), 256, 0, s>>>(acc, p.total_vars * kFeatAcc);
-    feature_count_kernel<<<grid_for(p.total_clauses, 256, 8192), 256, 0, s>>>(p.d_rec, p.d_clause_off, p.d_fd, p.F,
-                                                                             p.total_clauses, acc);
-    feature_finish_kernel<<<grid_for(p.total_vars, 256, 8192), 256, 0, s>>>(acc, p.total_vars, x);
+hipError_t launch_features(const Plan &p, uint16_t *x, hipStream_t s) {
+    const bool vec = (reinterpret_cast<uintptr_t>(x) & 15u) == 0;
+    feature_kernel<<<p.n_tiles, kFeatThreads, 0, s>>>(p.d_rec, p.d_fd, p.d_tile, x, vec);
     return hipGetLastError();
 }
 
@@ -455,14 +541,16 @@ hipError_t launch_weights_to_bf16(const hp_mlp &net, hipStream_t s) {
 
 hipError_t launch_init_chains(const Plan &p, const float *q, int chain_lo, int chain_hi, uint8_t *v, hipStream_t s) {
     if (chain_hi <= chain_lo) return hipSuccess;
-    dim3 grid(grid_for(p.total_vars, 256, 1024), chain_hi - chain_lo);
-    init_chains_kernel<<<grid, 256, 0, s>>>(q, p.d_var_off, p.F, p.total_vars, p.B, chain_lo,
-                                            (uint32_t)(p.seed & 0xffffffffu), (uint32_t)(p.seed >> 32), v);
+    // chains per thread: as many as leave about eight workgroups per CU
+    const int64_t want = (8 * (int64_t)p.cus + p.n_tiles - 1) / p.n_tiles;
+    dim3 grid(p.n_tiles, (unsigned)std::max<int64_t>(1, std::min<int64_t>(chain_hi - chain_lo, want)));
+    init_chains_kernel<<<grid, kTileGroups, 0, s>>>(q, p.d_fd, p.d_tile, p.B, chain_lo, chain_hi,
+                                                    (uint32_t)(p.seed & 0xffffffffu), (uint32_t)(p.seed >> 32), v);
     return hipGetLastError();
 }
 
 hipError_t launch_chain_mean(const Plan &p, const uint8_t *a, float *out, hipStream_t s) {
-    chain_mean_kernel<<<grid_for(p.total_vars, 256, 8192), 256, 0, s>>>(a, p.d_var_off, p.F, p.total_vars, p.B, out);
+    chain_mean_kernel<<<p.n_tiles, kTileGroups, 0, s>>>(a, p.d_fd, p.d_tile, p.B, out);
     return hipGetLastError();
 }
 
