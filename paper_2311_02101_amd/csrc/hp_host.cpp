@@ -59,6 +59,8 @@ void release(Plan *p) {
     (void)hipFree(p->d_work);
     (void)hipFree(p->d_work_fb);
     (void)hipFree(p->d_mg_cnt);
+    (void)hipFree(p->d_mg_bits);
+    (void)hipFree(p->d_ctile);
     (void)hipFree(p->d_mg_v);
     (void)hipFree(p->d_mg_nu);
     (void)hipFree(p->d_lits);
@@ -77,7 +79,7 @@ void release(Plan *p) {
     (void)hipFree(p->d_temp);
     (void)hipFree(p->d_fe);
     (void)hipFree(p->d_fe_chain);
-    (void)hipFree(p->d_temp_old);
+    (void)hipFree(p->d_temp_list);
     (void)hipFree(p->d_W);
     (void)hipFree(p->d_b);
     (void)hipFree(p->d_Wc);
@@ -698,6 +700,11 @@ hp_status hp_plan(hp_plan_t *out, const hp_cnf *cnf, const hp_rbm *rbm, const hp
         for (int32_t i = 0; i < fd[f].n; i += kTileVars) tiles.push_back({f, i});
     p->n_tiles = (int32_t)tiles.size();
     HP_TRY(upload(&p->d_tile, tiles, s), "upload variable tiles");
+    std::vector<ClauseTile> ctiles;
+    for (int f = 0; f < F; ++f)
+        for (int32_t c = 0; c < fd[f].c; c += kTileClauses) ctiles.push_back({f, c});
+    p->n_ctiles = (int32_t)ctiles.size();
+    HP_TRY(upload(&p->d_ctile, ctiles, s), "upload clause tiles");
     HP_TRY(upload(&p->d_W, Wv, s), "upload W_c");
     HP_TRY(upload(&p->d_b, bv, s), "upload b_c");
     if (clust) {

@@ -42,6 +42,12 @@ struct VarTile {
     int32_t f;
     int32_t i0;
 };
+// Records [c0, min(c0 + kTileClauses, C_f)) of formula f.
+constexpr int kTileClauses = 8192;
+struct ClauseTile {
+    int32_t f;
+    int32_t c0;
+};
 
 // Device tables prepared once per plan (per temperature tau):
 //   thr[tau][m][l] = ceil(2^24 * sigma(b_c[l] + sum_k W_c[k,l] * bit_k(m)))
@@ -253,8 +259,11 @@ struct Plan {
     WorkItem *d_work = nullptr;
     WorkItem *d_work_fb = nullptr;        // the same items in (formula, chain) order
     int32_t *d_mg_cnt = nullptr;          // merge: counts (current, returned), source rows
-    uint8_t *d_mg_v = nullptr;            // merge: staging of v and nu (allocated on first use)
+    uint32_t *d_mg_bits = nullptr;        // merge: assignments, 32 chains a word (allocated on first use)
+    uint8_t *d_mg_v = nullptr;            // merge: staging of v and nu (only above kMergeRows chains)
     unsigned char *d_mg_nu = nullptr;
+    ClauseTile *d_ctile = nullptr;        // [n_ctiles] clause tiles of all formulas, in order
+    int32_t n_ctiles = 0;
     uint16_t *d_lits = nullptr;
     uint32_t *d_csr_ptr = nullptr;
     uint32_t *d_occ = nullptr;
@@ -264,8 +273,8 @@ struct Plan {
     int32_t *d_tabflag = nullptr;
     int32_t *d_temp = nullptr;            // [F][B]
     double *d_fe = nullptr;               // replica exchange: [T][128] clause free energies,
-    double *d_fe_chain = nullptr;         //   [F][B][T] formula free energies,
-    int32_t *d_temp_old = nullptr;        //   [F][B] temperatures before the round
+    double *d_fe_chain = nullptr;         //   [F][B][kFeParts][2] partial formula free energies,
+    int32_t *d_temp_list = nullptr;       //   [F][B] chains by temperature
     double *d_W = nullptr;
     double *d_b = nullptr;
     DeviceTables tab;
@@ -338,6 +347,7 @@ hipError_t launch_init_chains(const Plan &p, const float *q, int chain_lo, int c
 hipError_t launch_chain_mean(const Plan &p, const uint8_t *a, float *out, hipStream_t s);
 hipError_t launch_merge(Plan &p, const hp_state &st, const uint8_t *cand, hipStream_t s);
 constexpr int kMaxTemperTemps = 16;
+constexpr int kFeParts = 8;               // replica exchange: workgroups per chain, at most
 hipError_t launch_temper(Plan &p, const hp_state &st, int parity, hipStream_t s);
 
 void set_error(const std::string &msg);

@@ -94,3 +94,21 @@ def test_alternating_run_matches_oracle(hip):
     assert np.max(np.abs(nu - ost.nu) / ost.nu) < 1e-12
     assert np.array_equal(plan.current_temps()[0], otemps)
     plan.free()
+
+
+# more chains than a wave lists at once, temperatures with unequal numbers of
+# chains, and chains whose clauses several workgroups share
+@pytest.mark.parametrize("n,B,n_temps", [(400, 130, 16), (2100, 3, 2), (701, 65, 5)])
+def test_round_with_many_chains_and_shared_clauses(hip, n, B, n_temps):
+    T = wl.random_formula(n, 9)
+    W, b, _ = wl.pretrained_rbm(7, wl.FSTAR_16[:n_temps])
+    temps = np.random.default_rng(n).integers(0, n_temps, B).astype(np.int32)
+    plan = hp.Plan([T], [n], W, b, chains=B, temps=temps, precision="f64", seed=9)
+    st = plan.new_state([wl.initial_state(B, n, 9)])
+    say(f"[temper] n={n} B={B} T={n_temps}")
+    for r in range(3):
+        plan.run(st, 1)
+        _sync()
+        _check_round(plan, st, [T], [n], W, b, r % 2, 9)
+    assert np.array_equal(np.sort(plan.current_temps()[0]), np.sort(temps))
+    plan.free()
