@@ -574,6 +574,7 @@ hp_status hp_plan(hp_plan_t *out, const hp_cnf *cnf, const hp_rbm *rbm, const hp
     e = hipDeviceGetAttribute(&p->cus, hipDeviceAttributeMultiprocessorCount, p->device);
     if (e != hipSuccess) { release(p); return hip_fail(e, "hipDeviceGetAttribute"); }
     e = set_kernel_lds_limits(max_lds);
+    if (e == hipSuccess) e = set_merge_lds_limit();
     if (e != hipSuccess) { release(p); return hip_fail(e, "hipFuncSetAttribute"); }
     for (Bucket &bk : p->buckets) {
         if (bk.kind == kBucketPull)

@@ -345,6 +345,7 @@ hipError_t launch_weights_to_bf16(const hp_mlp &net, hipStream_t s);
 hipError_t launch_init_chains(const Plan &p, const float *q, int chain_lo, int chain_hi, uint8_t *v,
                               hipStream_t s);
 hipError_t launch_chain_mean(const Plan &p, const uint8_t *a, float *out, hipStream_t s);
+hipError_t set_merge_lds_limit();           // once per plan
 hipError_t launch_merge(Plan &p, const hp_state &st, const uint8_t *cand, hipStream_t s);
 constexpr int kMaxTemperTemps = 16;
 constexpr int kFeParts = 8;               // replica exchange: workgroups per chain, at most

@@ -61,3 +61,36 @@ def test_initial_draws_and_means_at_tile_edges(hip, sizes, chains, lo, hi):
         want = v.sum(axis=0, dtype=np.int64).astype(np.float32) / np.float32(chains)
         assert np.array_equal(mean.cpu().numpy()[off[f]:off[f + 1]], want)
     plan.free()
+
+
+# exact: counts are integers and kept rows are copies.  Chains at the edges of
+# the 32-chain words and of the in-place permutation (256), columns at the edges
+# of its 64-column slabs, clauses at the edge of a tile of 8192
+@pytest.mark.parametrize("sizes,B,precision,alias", [([63, 64, 65], 1, "f64", False), ([1025, 9], 33, "f32", False),
+                                                     ([1366, 70], 64, "f64", True), ([100, 30], 256, "f32", False),
+                                                     ([40, 100], 257, "f64", False)])
+def test_merge_at_tile_edges(hip, sizes, B, precision, alias):
+    import torch
+    from oracle import up as U
+    tables = [wl.random_formula(n, 41, tag=f) for f, n in enumerate(sizes)]
+    plan = _plan(tables, sizes, B, seed=4, precision=precision)
+    st = plan.new_state([wl.initial_state(B, n, 4, tag=f) for f, n in enumerate(sizes)])
+    plan.run(st, 2)
+    torch.cuda.synchronize()
+    rng = np.random.default_rng(B)
+    before = [st.formula(f) for f in range(len(sizes))]
+    parts = [rng.integers(0, 2, (B, n)).astype(np.uint8) for n in sizes]
+    for f in range(len(sizes)):
+        parts[f][B // 2] = before[f][0][B // 3]          # equal counts
+    if alias:
+        parts = [x[0] for x in before]
+    cand = st.v if alias else torch.tensor(np.concatenate([c.ravel() for c in parts]), device="cuda")
+    say(f"[merge] sizes={sizes} B={B} {precision} alias={alias}")
+    plan.merge_candidates(st, cand)
+    torch.cuda.synchronize()
+    for f, n in enumerate(sizes):
+        want_v, want_nu = U.merge_topb(tables[f], n, before[f][0], before[f][1], parts[f])
+        v, nu, s_max, best = st.formula(f)
+        assert np.array_equal(v, want_v) and np.array_equal(nu, want_nu)
+        assert np.array_equal(s_max, before[f][2]) and np.array_equal(best, before[f][3])
+    plan.free()
