@@ -92,11 +92,18 @@ void release(Plan *p) {
 }
 
 
-// Variable groups (of 4) per thread whose variance EMA stays in registers:
-// 1, 2 (FP32 and FP64) or 4 (FP32), else 0 (EMA in global memory).  The
-// mixed-precision kernel keeps at most one group in registers (two spill
-// next to its MFMA operands); four FP64 groups spill.
-int vpt_for(int groups, int threads, bool mixed, bool fp64) {
+// Variables of a launch per thread (Bucket::vpt): 1, 2 (FP32 and FP64) or 4
+// (FP32) groups of 4 whose variance EMA stays in registers, else 0 (EMA in
+// global memory).  The mixed-precision kernel keeps at most one group in
+// registers (two spill next to its MFMA operands); four FP64 groups spill.
+// A launch that leaves every chain a CU of its own is bound by the latency of
+// a sweep, not by issue slots, so there a push workgroup with at least as many
+// threads as variables updates one variable per thread: four times the Philox
+// work, a quarter of the serial sigmoids (256 variables, 1024 threads, FP64: the
+// visible phase of a sweep 2800 -> 1000 cycles of 8000).
+int vpt_for(const Bucket &bk, int threads, int cus, bool mixed, bool fp64) {
+    const int groups = (bk.max_n + 3) / 4;
+    if (bk.max_n <= threads && bk.count <= cus && bk.kind != kBucketPull && !mixed) return kVptOne;
     if (groups <= threads) return 1;
     if (groups <= 2 * threads && !mixed) return 2;
     if (groups <= 4 * threads && !mixed && !fp64) return 4;
@@ -590,8 +597,7 @@ hp_status hp_plan(hp_plan_t *out, const hp_cnf *cnf, const hp_rbm *rbm, const hp
             while (t < kMaxThreads && t * 6 < bk.max_c) t *= 2;
         }
         bk.threads = t;
-        const int groups = (bk.max_n + 3) / 4;
-        bk.vpt = vpt_for(groups, t, mixed, opts->precision != HP_FP32);
+        bk.vpt = vpt_for(bk, t, p->cus, mixed, opts->precision != HP_FP32);
         // persistent grid when the items outnumber the resident workgroups
         const int occ = bucket_occupancy(*p, bk);
         const int64_t capacity = (int64_t)p->cus * std::max(occ, 1);
@@ -896,8 +902,7 @@ hp_status hp_tune(hp_plan_t plan, const hp_state *st, int64_t n_sweeps, void *st
                 bk.kind = kinds[ki];
                 bk.lds = lds_bytes_push(bk.max_n, bk.kind, &bk.v_off, &bk.x_off);
             }
-            const int groups = (bk.max_n + 3) / 4;
-            bk.vpt = vpt_for(groups, t, p->precision == HP_MIXED_BF16, p->precision != HP_FP32);
+            bk.vpt = vpt_for(bk, t, p->cus, p->precision == HP_MIXED_BF16, p->precision != HP_FP32);
             const int occ = bucket_occupancy(*p, bk);
             if (occ < 1) continue;     // this shape cannot launch
             const int64_t capacity = (int64_t)p->cus * occ;

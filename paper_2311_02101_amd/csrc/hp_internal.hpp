@@ -204,6 +204,12 @@ struct WorkQueue {
 enum BucketKind : int32_t { kBucketPush = 0, kBucketWide = 1, kBucketPull = 2, kBucketMid = 3 };
 constexpr int kMaxBuckets = 32;
 
+// Visible groups of four variables per thread whose variance average stays in
+// registers (VPT > 0); 0: any number, the average in global memory; kVptOne:
+// one variable per thread (the four threads of a group evaluate its Philox
+// block alike).
+constexpr int kVptOne = -1;
+
 struct Bucket {
     int32_t kind = kBucketPush;
     int32_t first = 0, count = 0;   // work items [first, first + count)

@@ -189,10 +189,16 @@ __device__ __forceinline__ Real ema(Real nu, Real rho, Real a) {
     return (one - a) * nu + a * rho * (one - rho);
 }
 
+// Sum over the wave, the same in every lane (row and quad permutes in the VALU;
+// shuffles through the LDS pipe take six dependent round trips).
 __device__ __forceinline__ int wave_sum(int x) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, kWave);
-    return x;
+    x += __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xf, 0xf, false);    // quad_perm 1,0,3,2
+    x += __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xf, 0xf, false);    // quad_perm 2,3,0,1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x141, 0xf, 0xf, false);   // row_half_mirror
+    x += __builtin_amdgcn_update_dpp(0, x, 0x140, 0xf, 0xf, false);   // row_mirror
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast15 into rows 1, 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast31 into rows 2, 3
+    return __builtin_amdgcn_readlane(x, kWave - 1);
 }
 
 size_t lds_bytes_pull(int max_n, int max_c, size_t real_bytes, int32_t *v_off, int32_t *hm_off) {
@@ -713,23 +719,27 @@ __device__ __forceinline__ void rec_load(const RecView &rv, int first, int lane,
 // simply take more steps and all of them reach the end of the clause phase
 // together (fixed shares left the youngest waves running alone at the end of
 // every clause phase).  The accumulators are exact integers, so which wave
-// takes which step does not change any result.  The counter hands out pairs
-// of consecutive steps (2j, 2j + 1): a wave goes to the counter only every
-// other step, so half as often waits for the add's result, whose wait also
-// covers the previous clause's accumulator atomics.  The counter runs on
-// across the sweeps of an item.  Of T steps (ceil(T/2) pairs) and W waves,
-// every wave takes one pair past the last one per sweep, except, for odd T,
+// takes which step does not change any result.  Steps go out in pairs of
+// consecutive ones (2j, 2j + 1): a wave goes to the counter only every other
+// step, so half as often waits for the add's result, whose wait also covers
+// the previous clause's accumulator atomics.  Wave w starts every sweep with
+// pair w, so its first records can be on their way before the sweep begins;
+// the pairs from W on (W waves) come from the counter, which runs on across
+// the sweeps of an item.  Of T steps (ceil(T/2) pairs) a wave with a first
+// pair takes pairs until it gets one past the last one, except, for odd T,
 // the wave holding the last pair, whose second number T already ends its
-// clause phase: sweep s of an item owns the pair numbers [s P, (s + 1) P)
-// with P = ceil(T/2) + W - (T mod 2).
+// clause phase: sweep s of an item owns the counter's numbers [s P, (s + 1) P)
+// with P = ceil(T/2) - (T mod 2) = floor(T/2).
 // With dyn == 0 the steps are dealt round-robin instead (step k to wave
 // k mod W, no counter): better when another workgroup shares the CU and
 // fills the SIMDs while this one waits at its barrier.
 struct StepCounter {
-    int base;                    // first pair number of this sweep
+    int base;                    // first counter number of this sweep
     int dyn;                     // 1: take steps from the counter; 0: round-robin
     int wave, nw;
 };
+
+__device__ __forceinline__ int first_step(const StepCounter &sc) { return sc.dyn ? 2 * sc.wave : sc.wave; }
 
 // LDS byte address of the step counter (word 62 of the layout's counts,
 // zeroed before an item's first sweep); the sweep kernels have no static
@@ -772,48 +782,9 @@ __device__ __forceinline__ int lds_fetch_add1_wave(uint32_t one) {
 
 template <int kAddr>
 __device__ __forceinline__ int take_step(const StepCounter &sc, int prev) {
-    if (!sc.dyn) return prev < 0 ? sc.wave : prev + sc.nw;
-    if (prev >= 0 && (prev & 1) == 0) return prev + 1;     // the second step of the pair
-    return 2 * (lds_fetch_add1_wave<kAddr>(1u) - sc.base);
-}
-
-// The steps [olo, ohi) of the run [lo, hi) of clauses of length LEN.  `k`
-// is the wave's current step number: if it is in this run, the wave
-// processes it and keeps taking steps until it gets one past the run, which
-// it leaves in `k` for the next run.  The next step's records are loaded
-// while the current ones are processed (two register sets, no copies).  The
-// load is issued on every iteration, past the run's end from the current
-// step again (its values are never used), so the wait for a step's records
-// counts the one load issued after them on every path.
-template <int LEN, bool kSample, bool kClust, int NB, int kTab>
-__device__ __forceinline__ int clause_segment(const PushLds &L, const RecView &rv, int lo, int hi, int olo, int ohi,
-                                              int &k, const StepCounter &sc, int lane, const PhiloxSweep &ps,
-                                              Key2 key, uint32_t nbh, uint32_t full, uint32_t lmask) {
-    int cnt = 0;
-    if (k >= ohi) return 0;
-    int base = lo + (k - olo) * kWave;
-    uint4 ra, rb;
-    uint32_t oa, ob;
-    rec_load(rv, base, lane, ra, oa);
-    for (;;) {
-        int kn = take_step<step_counter_addr<kTab, kClust>()>(sc, k);
-        int next = lo + (kn - olo) * kWave;
-        rec_load(rv, kn < ohi ? next : base, lane, rb, ob);
-        rec_hold(ra, oa);
-        if (lane < hi - base) clause_one<LEN, kSample, kClust, NB, kTab>(L, ra, oa, ps, key, nbh, full, lmask, cnt);
-        k = kn;
-        if (kn >= ohi) break;
-        base = next;
-        kn = take_step<step_counter_addr<kTab, kClust>()>(sc, k);
-        next = lo + (kn - olo) * kWave;
-        rec_load(rv, kn < ohi ? next : base, lane, ra, oa);
-        rec_hold(rb, ob);
-        if (lane < hi - base) clause_one<LEN, kSample, kClust, NB, kTab>(L, rb, ob, ps, key, nbh, full, lmask, cnt);
-        k = kn;
-        if (kn >= ohi) break;
-        base = next;
-    }
-    return cnt;
+    if (!sc.dyn) return prev + sc.nw;
+    if ((prev & 1) == 0) return prev + 1;     // the second step of the pair
+    return 2 * (sc.nw + lds_fetch_add1_wave<kAddr>(1u) - sc.base);
 }
 
 // steps of the runs of a range: o[k] = steps of the runs of lengths < k + 1
@@ -823,6 +794,90 @@ __device__ __forceinline__ void run_steps(const int32_t (&bnd)[8], int32_t (&o)[
     for (int k = 1; k < 8; ++k) o[k] = o[k - 1] + (bnd[k] - bnd[k - 1] + kWave - 1) / kWave;
 }
 
+// A wave's place in the clause phase: its current step k, whose records are in
+// (or on their way to) ra / oa, or rb / ob if odd is set.  The place is kept
+// from one length's run to the next and from one sweep to the next; `first`
+// is the first record of the wave's first step of a sweep.
+struct StepPipe {
+    int k, odd, first;
+    uint4 ra, rb;
+    uint32_t oa, ob;
+};
+
+// first record of step k, which lies in the run of length from + 1 or a later one
+__device__ __forceinline__ int step_base(const int32_t (&bnd)[8], const int32_t (&o)[8], int k, int from) {
+    int d = bnd[from] - o[from] * kWave;
+#pragma unroll
+    for (int j = from + 1; j < 7; ++j)
+        if (k >= o[j]) d = bnd[j] - o[j] * kWave;
+    return k * kWave + d;
+}
+
+// The steps of the run of clauses of length LEN.  If the wave's current step
+// is in this run, the wave processes it and keeps taking steps until it gets
+// one past the run, which the pipe carries to the next run.  The next step's
+// records are loaded while the current ones are processed (two register sets,
+// no copies), across the end of a run too, and behind the wave's last step of
+// the sweep those of its first step of the next sweep: a wave that waited for
+// the first records of every run lost an L2 round trip at each of up to six
+// lengths a sweep.  (With the barrier below: 128 formulas of 2048 variables x 32
+// chains x 50 sweeps, FP32, 10.9 -> 10.4 ms; 3001 variables x 32 chains, 8
+// workgroups each, size-clustered, 8.2 -> 6.8 us a sweep; 256 variables, one
+// chain, FP64, same shape, 6.0 -> 5.0 us.)  The load is issued on every
+// iteration, so the wait for a step's records counts the one load issued after
+// them on every path.
+template <int LEN, bool kSample, bool kClust, int NB, int kTab>
+__device__ __forceinline__ int clause_segment(const PushLds &L, const RecView &rv, const int32_t (&bnd)[8],
+                                              const int32_t (&o)[8], StepPipe &p, const StepCounter &sc, int lane,
+                                              const PhiloxSweep &ps, Key2 key, uint32_t nbh, uint32_t full,
+                                              uint32_t lmask) {
+    int cnt = 0;
+    const int ohi = o[LEN], hi = bnd[LEN];
+    if (p.k >= ohi) return 0;
+    int base = bnd[LEN - 1] + (p.k - o[LEN - 1]) * kWave;
+    int odd = p.odd;
+    for (;;) {
+        if (!odd) {
+            const int kn = take_step<step_counter_addr<kTab, kClust>()>(sc, p.k);
+            int next = bnd[LEN - 1] + (kn - o[LEN - 1]) * kWave;
+            if (kn >= ohi) next = LEN < 7 && kn < o[7] ? step_base(bnd, o, kn, LEN) : p.first;
+            rec_load(rv, next, lane, p.rb, p.ob);
+            rec_hold(p.ra, p.oa);
+            if (lane < hi - base)
+                clause_one<LEN, kSample, kClust, NB, kTab>(L, p.ra, p.oa, ps, key, nbh, full, lmask, cnt);
+            p.k = kn;
+            p.odd = 1;
+            if (kn >= ohi) break;
+            base = next;
+        }
+        odd = 0;
+        const int kn = take_step<step_counter_addr<kTab, kClust>()>(sc, p.k);
+        int next = bnd[LEN - 1] + (kn - o[LEN - 1]) * kWave;
+        if (kn >= ohi) next = LEN < 7 && kn < o[7] ? step_base(bnd, o, kn, LEN) : p.first;
+        rec_load(rv, next, lane, p.ra, p.oa);
+        rec_hold(p.rb, p.ob);
+        if (lane < hi - base)
+            clause_one<LEN, kSample, kClust, NB, kTab>(L, p.rb, p.ob, ps, key, nbh, full, lmask, cnt);
+        p.k = kn;
+        p.odd = 0;
+        if (kn >= ohi) break;
+        base = next;
+    }
+    return cnt;
+}
+
+// Starts the pipe of an item: loads the records of the wave's first step.
+__device__ __forceinline__ StepPipe start_pipe(const RecView &rv, const int32_t (&bnd)[8], const StepCounter &sc,
+                                               int lane) {
+    int32_t o[8];
+    run_steps(bnd, o);
+    StepPipe p{};
+    const int k = first_step(sc);
+    p.first = k < o[7] ? step_base(bnd, o, k, 0) : 0;
+    rec_load(rv, p.first, lane, p.ra, p.oa);
+    return p;
+}
+
 // Clause phase over the M records of a range (a formula's, or a split
 // member's run), sorted by clause length with bnd[k] = the number of records
 // of length <= k (bnd[0] = 0, bnd[7] = M).  The waves walk the records
@@ -830,16 +885,15 @@ __device__ __forceinline__ void run_steps(const int32_t (&bnd)[8], int32_t (&o)[
 // length (the gather and scatter unrolled for it) with no per-record length
 // test.  Returns this thread's number of satisfied clauses.
 template <bool kSample, bool kClust, int NB, int kTab>
-__device__ __forceinline__ int clause_phase_nb(const PushLds &L, const RecView &rv, const int32_t (&bnd)[8],
-                                               const StepCounter &sc, int lane, const PhiloxSweep &ps, Key2 key,
-                                               uint32_t nbh, uint32_t full, uint32_t lmask) {
+__device__ __forceinline__ int clause_phase(const PushLds &L, const RecView &rv, const int32_t (&bnd)[8],
+                                               StepPipe &p, const StepCounter &sc, int lane, const PhiloxSweep &ps,
+                                               Key2 key, uint32_t nbh, uint32_t full, uint32_t lmask) {
     int32_t o[8];
     run_steps(bnd, o);
     int cnt = 0;
-    int k = take_step<step_counter_addr<kTab, kClust>()>(sc, -1);
-#define HP_SEG(LEN)                                                                                              \
-    cnt += clause_segment<LEN, kSample, kClust, NB, kTab>(L, rv, bnd[LEN - 1], bnd[LEN], o[LEN - 1], o[LEN], k,  \
-                                                          sc, lane, ps, key, nbh, full, lmask)
+    p.k = first_step(sc);
+#define HP_SEG(LEN) \
+    cnt += clause_segment<LEN, kSample, kClust, NB, kTab>(L, rv, bnd, o, p, sc, lane, ps, key, nbh, full, lmask)
     HP_SEG(1);
     HP_SEG(2);
     HP_SEG(3);
@@ -852,22 +906,10 @@ __device__ __forceinline__ int clause_phase_nb(const PushLds &L, const RecView &
 }
 
 // counter numbers (pairs of steps) one sweep of a range consumes
-__device__ __forceinline__ int sweep_step_numbers(const int32_t (&bnd)[8], int NT) {
+__device__ __forceinline__ int sweep_step_numbers(const int32_t (&bnd)[8]) {
     int32_t o[8];
     run_steps(bnd, o);
-    return (o[7] + 1) / 2 + NT / kWave - (o[7] & 1);
-}
-
-template <bool kSample, bool kClust, int kTab>
-__device__ __forceinline__ int clause_phase(const PushLds &L, const uint4 *__restrict__ rec,
-                                            const uint32_t *__restrict__ orig, int M, const int32_t (&bnd)[8],
-                                            const StepCounter &sc, int tid, const PhiloxSweep &ps, Key2 key,
-                                            uint32_t nbh, uint32_t full, uint32_t lmask) {
-    const int lane = tid & (kWave - 1);
-    const RecView rv = rec_view(rec, orig, M);
-    if (kClust) return clause_phase_nb<kSample, kClust, 0, kTab>(L, rv, bnd, sc, lane, ps, key, nbh, full, lmask);
-    return nbh > 1 ? clause_phase_nb<kSample, kClust, 2, kTab>(L, rv, bnd, sc, lane, ps, key, nbh, full, lmask)
-                   : clause_phase_nb<kSample, kClust, 1, kTab>(L, rv, bnd, sc, lane, ps, key, nbh, full, lmask);
+    return o[7] / 2;
 }
 
 // Range-relative length bounds of split member g of G: the member's run
@@ -1049,14 +1091,165 @@ __device__ __forceinline__ uint8_t visible_update<float>(int64_t xi, double fx_s
     return (float)(word >> 8) < rho24 ? 1 : 0;
 }
 
-// workgroup total of a per-thread count (uses L.cnt; ends with a barrier)
-__device__ __forceinline__ int block_total(const PushLds &L, int cnt, int tid, int NT) {
+// Barrier of the workgroup that orders LDS accesses only.  The sweep loops
+// exchange nothing through global memory inside a workgroup (a thread reads
+// back only what it wrote), and __syncthreads() would also wait for every
+// global load and store in flight, the next records' loads among them (alone,
+// with loads it still waited for elsewhere, 1% on uneven batches).
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Workgroup total of a per-thread count in sweep s: every wave adds its sum to
+// one of two LDS words (by the sweep's parity), one barrier, one read.  The
+// other word, last read before the barrier that ended the previous sweep, is
+// cleared for the next one.  (A word per wave and a loop over them after the
+// barrier took 0.7 us of a 6 us sweep of the smallest formulas.)
+__device__ __forceinline__ int block_total(const PushLds &L, int cnt, int tid, int64_t s) {
+    const int slot = (int)(s & 1);
     cnt = wave_sum(cnt);
-    if ((tid & (kWave - 1)) == 0) L.cnt[tid / kWave] = cnt;
-    __syncthreads();
-    int total = 0;
-    for (int wv = 0; wv < NT / kWave; ++wv) total += L.cnt[wv];
-    return total;
+    if ((tid & (kWave - 1)) == 0) atomicAdd(&L.cnt[slot], cnt);
+    lds_barrier();
+    if (tid == 0) L.cnt[slot ^ 1] = 0;
+    return __builtin_amdgcn_readfirstlane(L.cnt[slot]);
+}
+
+// The chain a workgroup of the push launch is working on.
+template <typename Real>
+struct PushCtx {
+    PushLds L;
+    const uint4 *rec;
+    const uint32_t *orig;
+    const int32_t *negcnt;
+    int64_t sbase, S, t0;
+    Key2 key;
+    double fx_scale;
+    Real alpha;
+    int N, C, tid, NT, b, wave, dyn, K;
+    int steps;                   // step counter numbers per sweep
+    int32_t lofs[8];
+    uint32_t nbh, full, lmask;
+    bf16x8_t a1, a2;             // mixed precision: the products' constant operands
+};
+
+// All sweeps of one chain.  kSample, and the Philox blocks per clause NB, are
+// fixed for the whole loop: choosing them every sweep made the records on their
+// way (StepPipe) pass through copies, which wait for them, where the choices
+// join.
+template <typename Real, int VPT, int kTab, bool kMfma, bool kClust, bool kSample, int NB>
+__device__ __forceinline__ void push_sweeps(const SweepParams<Real> &P, const PushCtx<Real> &c,
+                                            Real (&nu)[VPT > 0 ? VPT : 1][VPT == kVptOne ? 1 : 4], int &smax) {
+    const PushLds &L = c.L;
+    const int N = c.N, tid = c.tid, NT = c.NT, lane = tid & (kWave - 1);
+    // buffer views of this chain's best and nu and the formula's negated-
+    // slot counts: the visible phase addresses them by the variable's
+    // offset alone (accesses past N read zeros and write nothing)
+    const __amdgpu_buffer_rsrc_t best_rs =
+        __builtin_amdgcn_make_buffer_rsrc(P.best + c.sbase, (short)0, N, kRawBufferWord3);
+    const __amdgpu_buffer_rsrc_t nu_rs =
+        __builtin_amdgcn_make_buffer_rsrc(P.nu + c.sbase, (short)0, N * (int)sizeof(Real), kRawBufferWord3);
+    const __amdgpu_buffer_rsrc_t neg_rs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(c.negcnt), (short)0, N * 4, kRawBufferWord3);
+    const RecView rv = rec_view(c.rec, c.orig, c.C);
+    auto step_counter = [&](int64_t s) { return StepCounter{(int)s * c.steps, c.dyn, c.wave, NT / kWave}; };
+    StepPipe pipe{};
+    if (!kMfma) pipe = start_pipe(rv, c.lofs, step_counter(0), lane);
+
+    for (int64_t s = 0; s < c.S; ++s) {
+        const uint64_t t = (uint64_t)(c.t0 + s);
+        const uint32_t tlo = (uint32_t)t, thi = (uint32_t)(t >> 32);
+        const PhiloxSweep ps = philox_sweep_consts(tlo, (uint32_t)c.b, thi, c.key);
+        int cnt;
+        if (kMfma)
+            cnt = clause_phase_mfma<kSample>(L, c.rec, c.orig, c.C, tid, NT, tlo, thi, (uint32_t)c.b, c.key, c.nbh, c.full,
+                                             c.lmask, c.K, c.a1, c.a2, 1.0 / c.fx_scale);
+        else
+            cnt = clause_phase<kSample, kClust, NB, kTab>(L, rv, c.lofs, pipe, step_counter(s), lane, ps, c.key, c.nbh,
+                                                          c.full, c.lmask);
+        // the thread index passes through an empty asm each sweep, so the
+        // per-variable offsets below are recomputed here instead of being
+        // hoisted out of the sweep loop into registers held across the
+        // clause phase
+        int vtid = tid;
+        asm volatile("" : "+v"(vtid));
+        // what the visible phase needs beyond the accumulators, on its way
+        // while the workgroup gathers at the barrier: the negated-slot counts
+        // (the accumulators restart there), and the random words where they
+        // are few
+        constexpr int VR = VPT > 0 ? VPT : 1;
+        // (two groups of FP64 averages leave no registers for the counts)
+        constexpr bool kEarly = VPT == 1 || VPT == kVptOne;
+        constexpr bool kNegEarly = kEarly || (VPT > 0 && sizeof(Real) == 4);
+        uint4 nc[VR];
+        uint4 rnd = make_uint4(0, 0, 0, 0);
+        if (kSample && kNegEarly) {
+            if (VPT == kVptOne) {
+                nc[0].x = __builtin_amdgcn_raw_buffer_load_b32(neg_rs, vtid * 4, 0, 0);
+            } else {
+#pragma unroll
+                for (int j = 0; j < VR; ++j) {
+                    const auto c4 = __builtin_amdgcn_raw_buffer_load_b128(neg_rs, (vtid + j * NT) * 16, 0, 0);
+                    nc[j] = make_uint4(c4[0], c4[1], c4[2], c4[3]);
+                }
+            }
+            if (kEarly) rnd = philox_sweep(kPhaseVisible | (uint32_t)(VPT == kVptOne ? vtid >> 2 : vtid), ps, c.key);
+        }
+        const int total = block_total(L, cnt, tid, s);
+        const bool improved = total > smax;
+        if (improved) smax = total;
+        // ---- visible phase ----
+        if (VPT == kVptOne) {
+            if (vtid < N) {
+                if (improved) __builtin_amdgcn_raw_buffer_store_b8(L.v[vtid], best_rs, vtid, 0, 0);
+                if (kSample) {
+                    const int q = vtid & 3;
+                    const uint32_t word = q == 0 ? rnd.x : q == 1 ? rnd.y : q == 2 ? rnd.z : rnd.w;
+                    const int64_t xi = L.x[vtid];
+                    L.x[vtid] = (int32_t)nc[0].x;
+                    L.v[vtid] = visible_update(xi, c.fx_scale, nu[0][0], c.alpha, word);
+                }
+            }
+        } else {
+            const int groups = (N + 3) >> 2;
+            const int jmax = VPT > 0 ? VPT : (groups + NT - 1) / NT;
+#pragma unroll
+            for (int j = 0; j < VR; ++j) {
+                for (int jj = (VPT > 0 ? j : 0); jj < (VPT > 0 ? j + 1 : jmax); ++jj) {
+                    const int grp = vtid + jj * NT;
+                    if (grp < groups) {
+                        uint4 r = rnd, n4 = nc[j];
+                        if (kSample && !kEarly) r = philox_sweep(kPhaseVisible | (uint32_t)grp, ps, c.key);
+                        if (kSample && !kNegEarly) {
+                            const auto c4 = __builtin_amdgcn_raw_buffer_load_b128(neg_rs, grp * 16, 0, 0);
+                            n4 = make_uint4(c4[0], c4[1], c4[2], c4[3]);
+                        }
+                        const uint32_t rw[4] = {r.x, r.y, r.z, r.w}, nw[4] = {n4.x, n4.y, n4.z, n4.w};
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const int i = grp * 4 + q;
+                            if (i < N) {
+                                if (improved) __builtin_amdgcn_raw_buffer_store_b8(L.v[i], best_rs, i, 0, 0);
+                                if (kSample) {
+                                    const int64_t xi = L.x[i];
+                                    L.x[i] = (int32_t)nw[q];
+                                    if (VPT > 0) {
+                                        L.v[i] = visible_update(xi, c.fx_scale, nu[j][q], c.alpha, rw[q]);
+                                    } else {
+                                        Real nv = buffer_load_real<Real>(nu_rs, i);
+                                        L.v[i] = visible_update(xi, c.fx_scale, nv, c.alpha, rw[q]);
+                                        buffer_store_real(nv, nu_rs, i);
+                                    }
+                                }
+                            }
+                        }
+                    }
+                }
+            }
+        }
+        lds_barrier();
+    }
 }
 
 // One chain per workgroup at a time.  Q.ctr == nullptr: workgroup w runs
@@ -1081,8 +1274,6 @@ __global__ __launch_bounds__(1024) void sweep_push_kernel(SweepParams<Real> P, W
     const uint32_t nbh = (uint32_t)(P.L + 3) >> 2;
     const uint32_t full = (1u << P.K) - 1u;
     const uint32_t lmask = (1u << P.L) - 1u;
-    const Real alpha = P.alpha;
-    const double fx_scale = P.fx_scale;
     const int64_t t0 = *P.t_ptr;
 
     const int home = (int)(blockIdx.x % kXcds);
@@ -1115,123 +1306,77 @@ __global__ __launch_bounds__(1024) void sweep_push_kernel(SweepParams<Real> P, W
         }
         const WorkItem w = P.work[item];
         const FormulaDev fd = P.fd[w.f];
-        const int N = fd.n, C = fd.c;
+        const int N = fd.n;
         const int tau = P.temp_of_chain[(int64_t)w.f * P.B + w.b];
-        const PushLds L = kClust ? push_lds_clust(lds, P.lds_x_off)
-                                 : push_lds_for<kTab>(lds, P.lds_x_off, P.gfx, tau);
         const int64_t sbase = fd.var_off * P.B + (int64_t)w.b * N;
-        const uint4 *__restrict__ rec = P.rec + fd.clause_off;
-        const uint32_t *__restrict__ orig = P.orig + fd.clause_off;
-        const Key2 key{P.key0, P.key1 ^ (uint32_t)w.f};
-        const int32_t *__restrict__ negcnt = P.negcnt + fd.var_off;
+        PushCtx<Real> c;
+        c.L = kClust ? push_lds_clust(lds, P.lds_x_off) : push_lds_for<kTab>(lds, P.lds_x_off, P.gfx, tau);
+        const PushLds &L = c.L;
+        c.rec = P.rec + fd.clause_off;
+        c.orig = P.orig + fd.clause_off;
+        c.negcnt = P.negcnt + fd.var_off;
+        c.sbase = sbase;
+        c.S = S;
+        c.t0 = t0;
+        c.key = Key2{P.key0, P.key1 ^ (uint32_t)w.f};
+        c.fx_scale = P.fx_scale;
+        c.alpha = P.alpha;
+        c.N = N;
+        c.C = fd.c;
+        c.tid = tid;
+        c.NT = NT;
+        c.b = w.b;
+        c.wave = wave_id;
+        c.dyn = P.dyn_steps;
+        c.K = P.K;
+        c.steps = sweep_step_numbers(fd.lofs);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) c.lofs[k] = fd.lofs[k];
+        c.nbh = nbh;
+        c.full = full;
+        c.lmask = lmask;
 
         load_push_tables<kTab, kClust>(L, P.thr, P.gfx, P.gpad, tau, tid, NT, full);
         for (int i = tid; i < N; i += NT) {
             L.v[i] = P.v[sbase + i];
-            L.x[i] = negcnt[i];
+            L.x[i] = c.negcnt[i];
         }
-        bf16x8_t a1 = {}, a2 = {};
+        c.a1 = c.a2 = bf16x8_t{};
         if (kMfma) {
-            a1 = __builtin_bit_cast(bf16x8_t, P.mfma[((size_t)tau * 2 + 0) * kWave + (tid & (kWave - 1))]);
-            a2 = __builtin_bit_cast(bf16x8_t, P.mfma[((size_t)tau * 2 + 1) * kWave + (tid & (kWave - 1))]);
+            c.a1 = __builtin_bit_cast(bf16x8_t, P.mfma[((size_t)tau * 2 + 0) * kWave + (tid & (kWave - 1))]);
+            c.a2 = __builtin_bit_cast(bf16x8_t, P.mfma[((size_t)tau * 2 + 1) * kWave + (tid & (kWave - 1))]);
         }
-        constexpr int VR = VPT > 0 ? VPT : 1;
-        Real nu[VR][4];
-        if (VPT > 0) {
+        // this thread's variables: 4 (tid + j NT) + q, or variable tid
+        constexpr int VR = VPT > 0 ? VPT : 1, VQ = VPT == kVptOne ? 1 : 4;
+        Real nu[VR][VQ];
+        if (VPT != 0) {
 #pragma unroll
             for (int j = 0; j < VR; ++j)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int i = (tid + j * NT) * 4 + q;
+                for (int q = 0; q < VQ; ++q) {
+                    const int i = (tid + j * NT) * VQ + q;
                     nu[j][q] = i < N ? P.nu[sbase + i] : Real(0);
                 }
         }
-        // buffer views of this chain's best and nu and the formula's negated-
-        // slot counts: the visible phase addresses them by the variable's
-        // offset alone (accesses past N read zeros and write nothing)
-        const __amdgpu_buffer_rsrc_t best_rs =
-            __builtin_amdgcn_make_buffer_rsrc(P.best + sbase, (short)0, N, kRawBufferWord3);
-        const __amdgpu_buffer_rsrc_t nu_rs =
-            __builtin_amdgcn_make_buffer_rsrc(P.nu + sbase, (short)0, N * (int)sizeof(Real), kRawBufferWord3);
-        const __amdgpu_buffer_rsrc_t neg_rs =
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(negcnt), (short)0, N * 4, kRawBufferWord3);
         int smax = P.s_max[(int64_t)w.f * P.B + w.b];
-        const int steps = sweep_step_numbers(fd.lofs, NT);     // step numbers per sweep
-        if (tid == 0) L.cnt[62] = 0;
+        if (tid == 0) L.cnt[0] = L.cnt[1] = L.cnt[62] = 0;
         __syncthreads();
 
-        for (int64_t s = 0; s < S; ++s) {
-            const uint64_t t = (uint64_t)(t0 + s);
-            const uint32_t tlo = (uint32_t)t, thi = (uint32_t)(t >> 32);
-            const PhiloxSweep ps = philox_sweep_consts(tlo, (uint32_t)w.b, thi, key);
-            int cnt;
-            if (kMfma)
-                cnt = sample ? clause_phase_mfma<true>(L, rec, orig, C, tid, NT, tlo, thi, (uint32_t)w.b, key, nbh, full,
-                                                       lmask, P.K, a1, a2, 1.0 / fx_scale)
-                             : clause_phase_mfma<false>(L, rec, orig, C, tid, NT, tlo, thi, (uint32_t)w.b, key, nbh,
-                                                        full, lmask, P.K, a1, a2, 1.0 / fx_scale);
-            else
-            {
-                const StepCounter sc{(int)s * steps, P.dyn_steps, wave_id, NT / kWave};
-                cnt = sample ? clause_phase<true, kClust, kTab>(L, rec, orig, C, fd.lofs, sc, tid, ps, key, nbh, full, lmask)
-                             : clause_phase<false, kClust, kTab>(L, rec, orig, C, fd.lofs, sc, tid, ps, key, nbh, full, lmask);
-            }
-            const int total = block_total(L, cnt, tid, NT);
-            const bool improved = total > smax;
-            if (improved) smax = total;
-            // ---- visible phase ----
-            const int groups = (N + 3) >> 2;
-            const int jmax = VPT > 0 ? VPT : (groups + NT - 1) / NT;
-            // the thread index passes through an empty asm each sweep, so the
-            // per-variable offsets below are recomputed here instead of being
-            // hoisted out of the sweep loop into registers held across the
-            // clause phase
-            int vtid = tid;
-            asm volatile("" : "+v"(vtid));
-#pragma unroll
-            for (int j = 0; j < (VPT > 0 ? VPT : 1); ++j) {
-              for (int jj = (VPT > 0 ? j : 0); jj < (VPT > 0 ? j + 1 : jmax); ++jj) {
-                const int grp = vtid + jj * NT;
-                if (grp < groups) {
-                    uint4 r = make_uint4(0, 0, 0, 0);
-                    int32_t nc[4] = {0, 0, 0, 0};
-                    if (sample) {
-                        r = philox_sweep(kPhaseVisible | (uint32_t)grp, ps, key);
-                        // the accumulators restart at the negated-slot counts
-                        const auto c4 = __builtin_amdgcn_raw_buffer_load_b128(neg_rs, grp * 16, 0, 0);
-                        nc[0] = (int32_t)c4[0], nc[1] = (int32_t)c4[1], nc[2] = (int32_t)c4[2], nc[3] = (int32_t)c4[3];
-                    }
-                    const uint32_t rw[4] = {r.x, r.y, r.z, r.w};
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int i = grp * 4 + q;
-                        if (i < N) {
-                            if (improved) __builtin_amdgcn_raw_buffer_store_b8(L.v[i], best_rs, i, 0, 0);
-                            if (sample) {
-                                const int64_t xi = L.x[i];
-                                L.x[i] = nc[q];
-                                if (VPT > 0) {
-                                    L.v[i] = visible_update(xi, fx_scale, nu[j][q], alpha, rw[q]);
-                                } else {
-                                    Real nv = buffer_load_real<Real>(nu_rs, i);
-                                    L.v[i] = visible_update(xi, fx_scale, nv, alpha, rw[q]);
-                                    buffer_store_real(nv, nu_rs, i);
-                                }
-                            }
-                        }
-                    }
-                }
-              }
-            }
-            __syncthreads();
-        }
+        constexpr int NB = kClust ? 0 : 2;
+        if (!sample)
+            push_sweeps<Real, VPT, kTab, kMfma, kClust, false, NB>(P, c, nu, smax);
+        else if (kMfma || kClust || nbh > 1)
+            push_sweeps<Real, VPT, kTab, kMfma, kClust, true, NB>(P, c, nu, smax);
+        else
+            push_sweeps<Real, VPT, kTab, kMfma, kClust, true, kClust ? 0 : 1>(P, c, nu, smax);
+
         for (int i = tid; i < N; i += NT) P.v[sbase + i] = L.v[i];
-        if (VPT > 0) {
+        if (VPT != 0) {
 #pragma unroll
             for (int j = 0; j < VR; ++j)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int i = (tid + j * NT) * 4 + q;
+                for (int q = 0; q < VQ; ++q) {
+                    const int i = (tid + j * NT) * VQ + q;
                     if (i < N) P.nu[sbase + i] = nu[j][q];
                 }
         }
@@ -1291,7 +1436,6 @@ struct SplitCtx {
     int32_t bnd[8];              // its records of length <= k, k = 0..7 (run-relative)
     int steps;                   // clause-phase step numbers per sweep
     uint32_t nbh, full, lmask;
-    bool sample;
 };
 
 // Mailboxes of the exchange.  Every exchanged value carries a 2-bit tag, the
@@ -1346,7 +1490,7 @@ __device__ __forceinline__ T await_tag(const T *p, T e, uint32_t want, TagOf tag
 // thread (variable own_lo + tid + j NT, j < VPT): the four threads of a group
 // evaluate the group's Philox block alike and each takes its own word, and
 // the group's first thread packs the four new values into the published word.
-template <typename Real, int VPT, bool kClust>
+template <typename Real, int VPT, bool kClust, bool kSample, int NB>
 __device__ __forceinline__ void split_sweeps(const SweepParams<Real> &P, const SplitParams &Q, const SplitCtx<Real> &c,
                                              Real (&nu)[VPT > 0 ? VPT : 1], const int32_t (&ncr)[VPT > 0 ? VPT : 1],
                                              int &smax) {
@@ -1354,6 +1498,12 @@ __device__ __forceinline__ void split_sweeps(const SweepParams<Real> &P, const S
     const int G = c.G, g = c.g, N = c.N, tid = c.tid, NT = c.NT;
     const int own_lo = c.q_lo * 4, own_hi = min(N, c.q_hi * 4);
     const int jmax = VPT > 0 ? VPT : (own_hi - own_lo + NT - 1) / NT;
+    const int lane = tid & (kWave - 1);
+    const RecView rv = rec_view(c.rec + c.c_lo, c.orig + c.c_lo, c.c_hi - c.c_lo);
+    auto step_counter = [&](int64_t s) {
+        return StepCounter{(int)s * c.steps, 1, __builtin_amdgcn_readfirstlane(tid / kWave), NT / kWave};
+    };
+    StepPipe pipe = start_pipe(rv, c.bnd, step_counter(0), lane);
     for (int64_t s = 0; s < c.S; ++s) {
         const uint64_t t = (uint64_t)(c.t0 + s);
         const uint32_t tlo = (uint32_t)t, thi = (uint32_t)(t >> 32);
@@ -1361,15 +1511,11 @@ __device__ __forceinline__ void split_sweeps(const SweepParams<Real> &P, const S
         // member g's records: every G-th of the length-sorted order (the same
         // mix of clause lengths for all members), stored as one contiguous run
         const PhiloxSweep ps = philox_sweep_consts(tlo, (uint32_t)c.b, thi, c.key);
-        const StepCounter sc{(int)s * c.steps, 1, __builtin_amdgcn_readfirstlane(tid / kWave),
-                             NT / kWave};
-        const int cnt = c.sample ? clause_phase<true, kClust, kBucketPush>(L, c.rec + c.c_lo, c.orig + c.c_lo, c.c_hi - c.c_lo,
-                                                              c.bnd, sc, tid, ps, c.key, c.nbh, c.full, c.lmask)
-                                 : clause_phase<false, kClust, kBucketPush>(L, c.rec + c.c_lo, c.orig + c.c_lo, c.c_hi - c.c_lo,
-                                                               c.bnd, sc, tid, ps, c.key, c.nbh, c.full, c.lmask);
-        const int part = block_total(L, cnt, tid, NT);
+        const int cnt = clause_phase<kSample, kClust, NB, kBucketPush>(L, rv, c.bnd, pipe, step_counter(s), lane, ps, c.key,
+                                                                       c.nbh, c.full, c.lmask);
+        const int part = block_total(L, cnt, tid, s);
         // publish the partial logits of the variables other members own
-        if (c.sample) {
+        if (kSample) {
             for (int i = tid; i < N; i += NT) {
                 if (i >= own_lo && i < own_hi) continue;
                 xstore(&c.xpart[(size_t)g * c.nstride + i], L.x[i] ^ ((int64_t)tag << 61));
@@ -1386,14 +1532,13 @@ __device__ __forceinline__ void split_sweeps(const SweepParams<Real> &P, const S
         // lane k < G of every wave fetches member k's count and the wave sums
         // them (one load per member and wave, not per thread)
         auto await_total = [&]() {
-            const int lane = tid & (kWave - 1);
             int mine = 0;
             if (lane < G)
                 mine = lane == g ? part : (await_tag(&pc[lane], xload(&pc[lane]), ctag, tag_c, Q.err, Q.wait_limit) & kCntMask);
             return wave_sum(mine);
         };
         bool improved = false;
-        if (!kLateCount || !c.sample) {
+        if (!kLateCount || !kSample) {
             const int total = await_total();
             improved = total > smax;
             if (improved) smax = total;
@@ -1409,7 +1554,7 @@ __device__ __forceinline__ void split_sweeps(const SweepParams<Real> &P, const S
                 if (VPT > 0) oldv[j] = act ? L.v[i] : 0;
                 if (act) {
                     if (improved) P.best[c.sbase + i] = L.v[i];
-                    if (c.sample) {
+                    if (kSample) {
                         const uint4 r = philox_sweep(kPhaseVisible | (uint32_t)(i >> 2), ps, c.key);
                         const int q = i & 3;
                         const uint32_t word = q == 0 ? r.x : q == 1 ? r.y : q == 2 ? r.z : r.w;
@@ -1443,7 +1588,7 @@ __device__ __forceinline__ void split_sweeps(const SweepParams<Real> &P, const S
                         L.v[i] = (uint8_t)nvb;
                     }
                 }
-                if (c.sample) {
+                if (kSample) {
                     // own_lo and NT are multiples of 4: thread tid holds word i & 3 = tid & 3
                     const uint32_t b1 = __shfl_down(nvb, 1, kWave), b2 = __shfl_down(nvb, 2, kWave),
                                    b3 = __shfl_down(nvb, 3, kWave);
@@ -1452,7 +1597,7 @@ __device__ __forceinline__ void split_sweeps(const SweepParams<Real> &P, const S
                 }
             }
         }
-        if (kLateCount && c.sample) {
+        if (kLateCount && kSample) {
             const int total = await_total();
             if (total > smax) {
                 smax = total;
@@ -1463,7 +1608,7 @@ __device__ __forceinline__ void split_sweeps(const SweepParams<Real> &P, const S
                 }
             }
         }
-        if (c.sample) {
+        if (kSample) {
             for (int q = tid; q < c.groups; q += NT) {
                 if (q >= c.q_lo && q < c.q_hi) continue;
                 const uint32_t word = await_tag(&c.vbuf[q], xload(&c.vbuf[q]), tag, tag_v, Q.err, Q.wait_limit);
@@ -1471,7 +1616,7 @@ __device__ __forceinline__ void split_sweeps(const SweepParams<Real> &P, const S
                 for (int k = 0; k < 4; ++k)
                     if (q * 4 + k < N) L.v[q * 4 + k] = (uint8_t)((word >> (8 * k)) & 1u);
             }
-            __syncthreads();
+            lds_barrier();
         }
     }
 }
@@ -1510,7 +1655,7 @@ __global__ __launch_bounds__(1024) void sweep_split_kernel(SweepParams<Real> P, 
     c.c_lo = g * (fd.c / G) + min(g, fd.c % G);
     c.c_hi = c.c_lo + fd.c / G + (g < fd.c % G ? 1 : 0);
     member_bounds(fd.lofs, g, G, c.bnd);
-    c.steps = sweep_step_numbers(c.bnd, NT);
+    c.steps = sweep_step_numbers(c.bnd);
     c.tid = tid;
     c.NT = NT;
     c.b = w.b;
@@ -1518,8 +1663,7 @@ __global__ __launch_bounds__(1024) void sweep_split_kernel(SweepParams<Real> P, 
     c.rec = P.rec + fd.clause_off;
     c.orig = P.orig + fd.clause_off;
     c.key = Key2{P.key0, P.key1 ^ (uint32_t)w.f};
-    c.sample = P.n_sweeps > 0;
-    c.S = c.sample ? P.n_sweeps : 1;
+    c.S = P.n_sweeps > 0 ? P.n_sweeps : 1;
     c.nbh = (uint32_t)(P.L + 3) >> 2;
     c.full = (1u << P.K) - 1u;
     c.lmask = (1u << P.L) - 1u;
@@ -1555,10 +1699,15 @@ __global__ __launch_bounds__(1024) void sweep_split_kernel(SweepParams<Real> P, 
     }
     int smax = P.s_max[(int64_t)w.f * P.B + w.b];
     c.t0 = *P.t_ptr;
-    if (tid == 0) L.cnt[62] = 0;           // the clause-phase step counter
+    if (tid == 0) L.cnt[0] = L.cnt[1] = L.cnt[62] = 0;   // counts, clause-phase step counter
     __syncthreads();
 
-    split_sweeps<Real, VPT, kClust>(P, Q, c, nu, ncr, smax);
+    if (P.n_sweeps <= 0)
+        split_sweeps<Real, VPT, kClust, false, kClust ? 0 : 2>(P, Q, c, nu, ncr, smax);
+    else if (kClust || c.nbh > 1)
+        split_sweeps<Real, VPT, kClust, true, kClust ? 0 : 2>(P, Q, c, nu, ncr, smax);
+    else
+        split_sweeps<Real, VPT, kClust, true, kClust ? 0 : 1>(P, Q, c, nu, ncr, smax);
 
     // write back the owned part of the state
     for (int i = own_lo + tid; i < own_hi; i += NT) P.v[c.sbase + i] = L.v[i];
@@ -1624,9 +1773,10 @@ hipError_t launch_zero(uint32_t *ptr, int64_t n, hipStream_t s) {
 template <typename Real, int kTab>
 const void *push_kernel_ptr_t(int vpt) {
     switch (vpt) {
+        case kVptOne: return (const void *)sweep_push_kernel<Real, kVptOne, kTab>;
         case 1: return (const void *)sweep_push_kernel<Real, 1, kTab>;
         case 2: return (const void *)sweep_push_kernel<Real, 2, kTab>;
-        case 4: return (const void *)sweep_push_kernel<Real, 4, kTab>;
+        case 4: return (const void *)sweep_push_kernel<Real, sizeof(Real) == 4 ? 4 : 0, kTab>;   // FP32 only
         default: return (const void *)sweep_push_kernel<Real, 0, kTab>;
     }
 }
@@ -1642,9 +1792,10 @@ const void *push_kernel_ptr(int vpt, int kind) {
 template <typename Real>
 const void *clust_kernel_ptr(int vpt) {
     switch (vpt) {
+        case kVptOne: return (const void *)sweep_push_kernel<Real, kVptOne, kBucketPush, false, true>;
         case 1: return (const void *)sweep_push_kernel<Real, 1, kBucketPush, false, true>;
         case 2: return (const void *)sweep_push_kernel<Real, 2, kBucketPush, false, true>;
-        case 4: return (const void *)sweep_push_kernel<Real, 4, kBucketPush, false, true>;
+        case 4: return (const void *)sweep_push_kernel<Real, sizeof(Real) == 4 ? 4 : 0, kBucketPush, false, true>;
         default: return (const void *)sweep_push_kernel<Real, 0, kBucketPush, false, true>;
     }
 }
@@ -1681,7 +1832,7 @@ const void *pull_kernel_ptr(int vpt) {
 template <typename Real>
 hipError_t set_limits_t(int bytes) {
     std::vector<const void *> ks;
-    for (int vpt : {0, 1, 2, 4}) {
+    for (int vpt : {kVptOne, 0, 1, 2, 4}) {
         for (int kind : {(int)kBucketPush, (int)kBucketWide, (int)kBucketMid}) ks.push_back(push_kernel_ptr<Real>(vpt, kind));
         ks.push_back(clust_kernel_ptr<Real>(vpt));
     }

@@ -1,0 +1,38 @@
+"""Launch shapes of the sweep kernels where they can go wrong: one variable per
+thread (formulas up to the workgroup's size, on either side of the edge), and
+clause phases of few steps for many waves (waves with no step, an odd last one)."""
+import numpy as np
+import pytest
+
+from oracle import rbmsat as R
+from paper_2311_02101_amd import hp, workload as wl
+from tests.parity import compare_state, f64_bounds, say, teacher_forced_sweep
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,k,chains,threads,precision", [
+    (7, 7, 2, 1024, "f64"), (63, 7, 1, 64, "f64"), (64, 7, 3, 64, "f32"), (65, 7, 3, 64, "f64"),
+    (255, 3, 2, 256, "f32"), (1024, 7, 1, 1024, "f32"), (1024, 3, 2, 1024, "f64"), (1025, 7, 1, 1024, "f64"),
+    (130, 7, 300, 256, "f64")])
+def test_small_formulas_on_many_threads(hip, n, k, chains, threads, precision):
+    T = wl.random_formula(n, 51, k=k, lengths=[1, 2, 3] if k == 3 else wl.LENGTHS,
+                          probs=[0.2, 0.5, 0.3] if k == 3 else wl.LENGTH_PROBS)
+    W, b, _ = wl.pretrained_rbm(k, wl.FSTAR_PAIR)
+    temps = wl.default_temperatures(chains, 2)
+    v0 = wl.initial_state(chains, n, 51)
+    plan = hp.Plan([T], [n], W, b, chains=chains, temps=temps, precision=precision, seed=51, threads=threads, split=1)
+    st = plan.new_state([v0])
+    op, ost = R.plan(T, n, W, b), R.initial(v0)
+    say(f"[shapes] n={n} k={k} chains={chains} threads={threads} {precision}")
+    if precision == "f32":
+        for _ in range(4):
+            teacher_forced_sweep(plan, st, 0, ost, op, temps, alpha=1e-3, seed=51, prec="f32")
+    else:
+        for S in (5, 0, 7):                      # the pipe restarts with every run
+            plan.run(st, S)
+            if S:
+                ost = R.run(ost, op, temps, S, alpha=1e-3, seed=51)
+        compare_state(st.formula(0), (ost.v, ost.nu, ost.s_max, ost.best), "f64", f"n={n}",
+                      f64_bounds(plan, [T])[1])
+    plan.free()
