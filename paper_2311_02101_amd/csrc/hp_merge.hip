@@ -37,16 +37,27 @@ __global__ __launch_bounds__(kPackThreads) void pack_kernel(const FormulaDev *__
     const int g = (int)blockIdx.y, nb = min(32, B - 32 * g);
     const uint8_t *p = (blockIdx.z ? v_ret : v_cur) + off * B + (int64_t)g * 32 * n + i;
     uint32_t w[4] = {0u, 0u, 0u, 0u};
-#pragma unroll 8
-    for (int b = 0; b < nb; ++b) {
-        uint32_t x = 0;
-        if (m == 4) {
-            __builtin_memcpy(&x, p + (int64_t)b * n, 4);
-        } else {
-            for (int k = 0; k < m; ++k) x |= (uint32_t)p[(int64_t)b * n + k] << (8 * k);
-        }
+    auto add = [&](uint32_t x, int b) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) w[k] |= ((x >> (8 * k)) & 1u) << b;
+    };
+    if (m == 4) {
+        // 16 loads in flight (rows past the last chain read the last one again)
+#pragma unroll
+        for (int b0 = 0; b0 < 32; b0 += 16) {
+            if (b0 >= nb) break;
+            uint32_t x[16];
+#pragma unroll
+            for (int b = 0; b < 16; ++b) __builtin_memcpy(&x[b], p + (int64_t)min(b0 + b, nb - 1) * n, 4);
+#pragma unroll
+            for (int b = 0; b < 16; ++b) add(x[b], b0 + b);
+        }
+    } else {
+        for (int b = 0; b < nb; ++b) {
+            uint32_t x = 0;
+            for (int k = 0; k < m; ++k) x |= (uint32_t)p[(int64_t)b * n + k] << (8 * k);
+            add(x, b);
+        }
     }
     uint32_t *out = bits + ((int64_t)blockIdx.z * gridDim.y + g) * nv + off + i;
     for (int k = 0; k < m; ++k) out[k] = w[k];
