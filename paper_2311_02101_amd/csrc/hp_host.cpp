@@ -110,6 +110,54 @@ int vpt_for(const Bucket &bk, int threads, int cus, bool mixed, bool fp64) {
     return 0;
 }
 
+// Default shape of a push launch of the table models (the autotuner refines
+// it): table layout, workgroup size, step scheduling.  Every shape computes
+// the same bits.  Where the lines lie, from sweeps of 64..8000 variables x
+// 1..4200 chains (us per sweep, MI355X):
+//  * layout: contribution rows read from global memory (wide) wherever all
+//    tables would fit in LDS too: the rows of two temperatures (64 KB) stay in
+//    the caches, their reads leave the LDS pipe to gathers and accumulators,
+//    and less LDS admits more workgroups per CU.  Same 1024 threads, 256
+//    chains: 2000 variables 15.7 -> 13.9, 8000 56 -> 47; with the workgroups it
+//    admits, 4160 chains of 1000 variables 135 -> 94.
+//  * one chain per CU or fewer: as many threads as clauses, up to 1024 (64
+//    variables 6.0 -> 2.2, 256 variables 5.1 -> 2.9: a sweep there is a chain
+//    of latencies that more waves walk side by side).
+//  * m chains per CU: the most threads that keep m workgroups resident
+//    (registers hold about 1536 threads in FP32, 1280 in FP64): 300 chains of
+//    600 variables 11.9 (1024, two rounds) -> 9.0 (512).
+//  * crowded: about 6.5 sqrt(C) threads in FP32 (128 at 64 variables, 256 at
+//    256, 512 from 1000 up), fewer in FP64, whose registers hold fewer waves:
+//    fewer idle lanes in the last step of each clause length and fewer waves
+//    per barrier against fewer workgroups in flight (2000 variables, 4160
+//    chains, FP64: 512 threads 224, 256 threads 203).
+//  * steps from the counter where nothing else fills the CU at the barrier
+//    (four steps per wave up), or from sixty steps per wave up; else
+//    round-robin (512 variables, 1088 chains, FP64 21.4 -> 19.7).
+void default_shape(const Plan &p, Bucket &bk, int threads, int max_lds, bool clust, bool fp64) {
+    if (!clust && bk.kind == kBucketPush) bk.kind = kBucketWide;
+    bk.lds = clust ? lds_bytes_clust(bk.max_n, &bk.v_off, &bk.x_off)
+                   : lds_bytes_push(bk.max_n, bk.kind, &bk.v_off, &bk.x_off);
+    if (threads == 0) {
+        const int m = (bk.count + p.cus - 1) / p.cus;                  // chains per CU
+        const int r = std::max(1, (int)((size_t)max_lds / bk.lds));    // workgroups per CU that LDS admits
+        const int res = fp64 && bk.max_c < 3000 ? 1280 : 1536;
+        const int top = fp64 && r > 3 ? 256 : 512;
+        int crowded = 64;
+        while (crowded < top && crowded * 1.4142 < (fp64 ? 5.0 : 6.5) * std::sqrt((double)bk.max_c)) crowded *= 2;
+        int fill = kMaxThreads;
+        // (a few workgroups per CU of a large formula only pay over several rounds)
+        if (r > 3 || (r == 3 && m > 2) || (r == 2 && m > 3 && !fp64))
+            while (fill > kWave && std::min(m, r) * fill > res) fill /= 2;
+        threads = std::max(crowded, fill);
+        while (threads > kWave && threads / 4 >= bk.max_c) threads /= 2;
+    }
+    bk.threads = threads;
+    bk.vpt = vpt_for(bk, threads, p.cus, false, fp64);
+    const bool alone = bk.count <= p.cus || 2 * bk.lds > (size_t)max_lds || threads == kMaxThreads;
+    bk.dyn = bk.max_c >= (alone ? 4 : 60) * threads ? 1 : 0;
+}
+
 // Split a column of 8 weights into kLimbs BF16 limbs on the column's common
 // exponent grid (see the mixed-precision operand layout): limb j of entry i
 // is q * 2^(E - 8(j+1)) with |q| <= 256, rounded to nearest from what the
@@ -578,26 +626,29 @@ hp_status hp_plan(hp_plan_t *out, const hp_cnf *cnf, const hp_rbm *rbm, const hp
         bk.xq[kXcds] = pos - bk.first;
     }
     p->n_work = (int32_t)work.size();
+    std::vector<int> need;                // the layout each launch's largest tables need
+    for (const Bucket &bk : p->buckets) need.push_back(bk.kind);
     e = hipDeviceGetAttribute(&p->cus, hipDeviceAttributeMultiprocessorCount, p->device);
     if (e != hipSuccess) { release(p); return hip_fail(e, "hipDeviceGetAttribute"); }
     e = set_kernel_lds_limits(max_lds);
     if (e == hipSuccess) e = set_merge_lds_limit();
     if (e != hipSuccess) { release(p); return hip_fail(e, "hipFuncSetAttribute"); }
     for (Bucket &bk : p->buckets) {
-        if (bk.kind == kBucketPull)
-            bk.lds = lds_bytes_pull(bk.max_n, bk.max_c, real_bytes, &bk.v_off, &bk.hm_off);
-        else if (clust)
-            bk.lds = lds_bytes_clust(bk.max_n, &bk.v_off, &bk.x_off);
-        else
-            bk.lds = lds_bytes_push(bk.max_n, bk.kind, &bk.v_off, &bk.x_off);
-        // default workgroup size: about six clauses per thread per sweep
-        int t = opts->threads;
-        if (t == 0) {
-            t = 64;
-            while (t < kMaxThreads && t * 6 < bk.max_c) t *= 2;
+        if (bk.kind == kBucketPull || mixed) {
+            bk.lds = bk.kind == kBucketPull
+                         ? lds_bytes_pull(bk.max_n, bk.max_c, real_bytes, &bk.v_off, &bk.hm_off)
+                         : lds_bytes_push(bk.max_n, bk.kind, &bk.v_off, &bk.x_off);
+            // about six clauses per thread per sweep
+            int t = opts->threads;
+            if (t == 0) {
+                t = 64;
+                while (t < kMaxThreads && t * 6 < bk.max_c) t *= 2;
+            }
+            bk.threads = t;
+            bk.vpt = vpt_for(bk, t, p->cus, mixed, opts->precision != HP_FP32);
+        } else {
+            default_shape(*p, bk, opts->threads, max_lds, clust, opts->precision != HP_FP32);
         }
-        bk.threads = t;
-        bk.vpt = vpt_for(bk, t, p->cus, mixed, opts->precision != HP_FP32);
         // persistent grid when the items outnumber the resident workgroups
         const int occ = bucket_occupancy(*p, bk);
         const int64_t capacity = (int64_t)p->cus * std::max(occ, 1);
@@ -607,15 +658,20 @@ hp_status hp_plan(hp_plan_t *out, const hp_cnf *cnf, const hp_rbm *rbm, const hp
 
     // --- split: G co-resident workgroups per chain, single push bucket only ---
     int G = 1;
-    const bool single_push = p->buckets.size() == 1 && p->buckets[0].kind == kBucketPush;
-    if (opts->split >= 2 && !single_push) {
+    // (an explicit split asks for formulas whose tables would fit in LDS)
+    const bool one_push = p->buckets.size() == 1 && p->buckets[0].kind != kBucketPull && !mixed;
+    if (opts->split >= 2 && !(one_push && need[0] == kBucketPush)) {
         release(p);
         return fail(HP_EUNSUPPORTED, "split needs a batch whose formulas all share one push launch");
     }
-    if (single_push && opts->split != 1 && !opts->graph) {
+    if (one_push && opts->split != 1 && !opts->graph) {
         Bucket &bk = p->buckets[0];
-        const int saved = bk.threads;
+        const Bucket saved = bk;
         if (opts->threads == 0) bk.threads = kMaxThreads;
+        if (!clust) {
+            bk.kind = kBucketWide;        // the split kernel's table layout
+            bk.lds = lds_bytes_push(bk.max_n, bk.kind, &bk.v_off, &bk.x_off);
+        }
         // resident workgroups of the variant a split of G members launches
         auto capacity = [&](int G) { return (int64_t)p->cus * split_occupancy(*p, G); };
         const int n_items = bk.count;
@@ -637,13 +693,26 @@ hp_status hp_plan(hp_plan_t *out, const hp_cnf *cnf, const hp_rbm *rbm, const hp
                                                  std::to_string(capacity(G)) + ")");
             }
         } else {
-            // largest power of two that keeps every workgroup resident and
-            // leaves each member at least 1024 clauses
+            // The largest power of two that keeps every workgroup resident and
+            // leaves each member at least 1024 clauses, for formulas of enough
+            // work (a clause of one Philox block counts 0.6): 3000 clauses for
+            // four members, 4096 for two, whose exchange costs as much (us per
+            // sweep, 1 workgroup / split: 600 variables x 100 chains 5.1 / 5.3;
+            // 1027 x 32 7.9 / 5.3; 3 literals, 1027 x 128 5.0 / 5.4; 16384 x 64
+            // 84.8 / 40.6).  Sixteen members exchange more than they save unless
+            // they are few or have much to do each (8 / 16 members: 4096 x 16
+            // 7.9 / 8.5, 8192 x 16 11.3 / 12.1, 8192 x 3 11.2 / 10.2).
+            const double work_c = bk.max_c * (clust || L > 4 ? 1.0 : 0.6);
+            auto pays = [&](int g) {
+                return work_c >= 3000 && bk.max_c / g >= 1024 &&
+                       (g < 16 || (int64_t)n_items * g * 2 <= p->cus || bk.max_c / g >= 6144);
+            };
             while (G * 2 <= kMaxSplit && G * 2 <= min_groups && (int64_t)n_items * G * 2 <= capacity(G * 2) &&
-                   bk.max_c / (G * 2) >= 1024)
+                   pays(G * 2))
                 G *= 2;
+            if (G == 2 && work_c < 4096) G = 1;
         }
-        if (G == 1) bk.threads = saved;   // no split: keep the bucket's own shape
+        if (G == 1) bk = saved;           // no split: keep the bucket's own shape
         else bk.grid = 0;                 // split launches run one item per group
     }
     p->split = G;
