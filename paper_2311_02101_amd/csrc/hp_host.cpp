@@ -63,9 +63,9 @@ void release(Plan *p) {
     (void)hipFree(p->d_ctile);
     (void)hipFree(p->d_mg_v);
     (void)hipFree(p->d_mg_nu);
-    (void)hipFree(p->d_lits);
-    (void)hipFree(p->d_csr_ptr);
-    (void)hipFree(p->d_occ);
+    (void)hipFree(p->d_ell);
+    (void)hipFree(p->d_ell_slice);
+    (void)hipFree(p->d_ell_deg);
     (void)hipFree(p->d_rec);
     (void)hipFree(p->d_orig);
     (void)hipFree(p->d_negcnt);
@@ -96,14 +96,16 @@ void release(Plan *p) {
 // (FP32) groups of 4 whose variance EMA stays in registers, else 0 (EMA in
 // global memory).  The mixed-precision kernel keeps at most one group in
 // registers (two spill next to its MFMA operands); four FP64 groups spill.
+// The pull kernel keeps up to four variables per thread in registers.
 // A launch that leaves every chain a CU of its own is bound by the latency of
 // a sweep, not by issue slots, so there a push workgroup with at least as many
 // threads as variables updates one variable per thread: four times the Philox
 // work, a quarter of the serial sigmoids (256 variables, 1024 threads, FP64: the
 // visible phase of a sweep 2800 -> 1000 cycles of 8000).
 int vpt_for(const Bucket &bk, int threads, int cus, bool mixed, bool fp64) {
+    if (bk.kind == kBucketPull) return bk.max_n <= 4 * threads ? 4 : 0;
     const int groups = (bk.max_n + 3) / 4;
-    if (bk.max_n <= threads && bk.count <= cus && bk.kind != kBucketPull && !mixed) return kVptOne;
+    if (bk.max_n <= threads && bk.count <= cus && !mixed) return kVptOne;
     if (groups <= threads) return 1;
     if (groups <= 2 * threads && !mixed) return 2;
     if (groups <= 4 * threads && !mixed && !fp64) return 4;
@@ -351,15 +353,10 @@ hp_status hp_plan(hp_plan_t *out, const hp_cnf *cnf, const hp_rbm *rbm, const hp
 
     // --- per formula (independent, so formulas are packed on host threads):
     //   clause table: padding normalisation + packing (idx | neg << 15);
-    //   per-variable occurrence lists, (c, k) ascending (formula f's lists
-    //   start at K * clause_offset[f]: every clause has K slots);
-    //   push-kernel clause records: length, padding merge, sort by length.
+    //   clause records: length, padding merge, sort by length.
     //   len = K minus the trailing run of copies of literal 0 (the padding of
     //   Sec. 3.3); positions >= len contribute through the merged slot 0.
     std::vector<uint16_t> lits((size_t)K * NC);
-    std::vector<uint32_t> deg(NV, 0);
-    std::vector<uint32_t> csr_ptr(NV + F);
-    std::vector<uint32_t> occ((size_t)K * NC);
     std::vector<uint4> rec(NC);
     // orig[]: the first Philox block of each record's hidden draw (the
     // clause's input index times its blocks per clause, two in the
@@ -389,21 +386,8 @@ hp_status hp_plan(hp_plan_t *out, const hp_cnf *cnf, const hp_rbm *rbm, const hp
                 const int64_t a = x < 0 ? -(int64_t)x : (int64_t)x;
                 if (a > n) return "literal " + std::to_string(x) + " exceeds N_f";
                 lits[(size_t)k * NC + c] = (uint16_t)((a - 1) | (x < 0 ? 0x8000u : 0u));
-                deg[v0 + a - 1]++;
             }
         }
-        uint64_t pos = (uint64_t)K * (uint64_t)c0;
-        for (int64_t i = 0; i < n; ++i) {
-            csr_ptr[v0 + f + i] = (uint32_t)pos;
-            pos += deg[v0 + i];
-        }
-        csr_ptr[v0 + f + n] = (uint32_t)pos;
-        std::vector<uint32_t> fill(csr_ptr.begin() + v0 + f, csr_ptr.begin() + v0 + f + n);
-        for (int64_t c = c0; c < c1; ++c)
-            for (int k = 0; k < K; ++k) {
-                const uint16_t e = lits[(size_t)k * NC + c];
-                occ[fill[e & 0x7fff]++] = ((uint32_t)(c - c0) << 4) | ((e >> 15) << 3) | (uint32_t)k;
-            }
         std::vector<std::pair<int, int64_t>> key;
         key.reserve(c1 - c0);
         for (int64_t c = c0; c < c1; ++c) {
@@ -447,8 +431,9 @@ hp_status hp_plan(hp_plan_t *out, const hp_cnf *cnf, const hp_rbm *rbm, const hp
         }
         return std::string();
     };
-    {
-        // contiguous runs of formulas of about equal clause counts per thread
+    // fn(f) for every formula, contiguous runs of about equal clause counts
+    // per thread
+    auto each_formula = [&](auto &&fn) {
         int nt = (int)std::min<unsigned>(16u, std::max(1u, std::thread::hardware_concurrency()));
         if (F < 2 || NC < (int64_t(1) << 16)) nt = 1;
         nt = std::min(nt, F);
@@ -460,7 +445,7 @@ hp_status hp_plan(hp_plan_t *out, const hp_cnf *cnf, const hp_rbm *rbm, const hp
             first[t] = f;
         }
         auto run = [&](int t) {
-            for (int f = first[t]; f < first[t + 1]; ++f) pack_err[f] = pack_formula(f);
+            for (int f = first[t]; f < first[t + 1]; ++f) fn(f);
         };
         if (nt == 1) {
             run(0);
@@ -469,9 +454,10 @@ hp_status hp_plan(hp_plan_t *out, const hp_cnf *cnf, const hp_rbm *rbm, const hp
             for (int t = 0; t < nt; ++t) pool.emplace_back(run, t);
             for (std::thread &th : pool) th.join();
         }
-        for (int f = 0; f < F; ++f)
-            if (!pack_err[f].empty()) return fail(HP_EINVAL, pack_err[f]);
-    }
+    };
+    each_formula([&](int f) { pack_err[f] = pack_formula(f); });
+    for (int f = 0; f < F; ++f)
+        if (!pack_err[f].empty()) return fail(HP_EINVAL, pack_err[f]);
     // fixed-point scale: every slot contributes at most Wsum = sum |W_c| in
     // magnitude, a variable has at most max_slots slots, so |x| * 2^S stays
     // below 2^61 when (bound + 1) * 2^S < 2^61 (the split exchange tags bits
@@ -504,7 +490,7 @@ hp_status hp_plan(hp_plan_t *out, const hp_cnf *cnf, const hp_rbm *rbm, const hp
         fd[f].c = (int32_t)(cnf->clause_offset[f + 1] - cnf->clause_offset[f]);
         fd[f].var_off = cnf->var_offset[f];
         fd[f].clause_off = cnf->clause_offset[f];
-        fd[f].ptr_off = cnf->var_offset[f] + f;
+        fd[f].slice_off = 0;
         for (int k = 0; k < 8; ++k) fd[f].lofs[k] = lofs[f][k];
     }
 
@@ -514,7 +500,7 @@ hp_status hp_plan(hp_plan_t *out, const hp_cnf *cnf, const hp_rbm *rbm, const hp
     p->precision = opts->precision;
     p->alpha = opts->alpha;
     p->seed = opts->seed;
-    p->total_vars = NV; p->total_clauses = NC; p->total_occ = (int64_t)K * NC;
+    p->total_vars = NV; p->total_clauses = NC;
     p->max_n = max_n; p->max_c = max_c;
     p->fx_shift = fx_shift;
     p->clust = clust ? 1 : 0;
@@ -567,6 +553,61 @@ hp_status hp_plan(hp_plan_t *out, const hp_cnf *cnf, const hp_rbm *rbm, const hp
                                              " B) with the requested kernel");
         }
         cls[f] = size_class(f);
+    }
+    // Occurrence lists of the pull formulas: per variable (c, k) ascending over
+    // all K slots (padding copies too: the pull sum adds them one by one),
+    // the lists of 64 consecutive variables interleaved.
+    std::vector<uint32_t> ell, ell_slice, ell_deg;
+    {
+        int64_t n_slices = 0;
+        for (int f = 0; f < F; ++f)
+            if (kind[f] == kBucketPull) {
+                fd[f].slice_off = n_slices;
+                n_slices += (fd[f].n + kWave - 1) / kWave + 1;   // one more offset than slices
+            }
+        ell_slice.assign(n_slices, 0);
+        ell_deg.assign((size_t)n_slices * kWave, 0);
+        each_formula([&](int f) {
+            if (kind[f] != kBucketPull) return;
+            uint32_t *deg = ell_deg.data() + fd[f].slice_off * kWave;
+            const int64_t c0 = fd[f].clause_off, c1 = c0 + fd[f].c;
+            for (int k = 0; k < K; ++k)
+                for (int64_t c = c0; c < c1; ++c) deg[lits[(size_t)k * NC + c] & 0x7fff]++;
+            const int sl = (fd[f].n + kWave - 1) / kWave;
+            for (int j = 0; j < sl; ++j) {
+                const uint32_t w = *std::max_element(deg + j * kWave, deg + (j + 1) * kWave);
+                ell_slice[fd[f].slice_off + j] = std::max(4u, (w + 3) / 4 * 4);
+            }
+        });
+        uint64_t pos = 0;                      // widths to offsets
+        for (uint32_t &w : ell_slice) {
+            const uint32_t width = w;
+            w = (uint32_t)pos;
+            pos += width;
+        }
+        if (pos >= (uint64_t(1) << 32)) {
+            release(p);
+            return fail(HP_EUNSUPPORTED, "too many clause slots");
+        }
+        try {                                  // 64 words per entry of a slice's longest list
+            ell.assign((size_t)pos * kWave, 0);
+        } catch (const std::bad_alloc &) {
+            release(p);
+            return fail(HP_ENOMEM, "host allocation failed");
+        }
+        each_formula([&](int f) {
+            if (kind[f] != kBucketPull) return;
+            const uint32_t *first = ell_slice.data() + fd[f].slice_off;
+            std::vector<uint32_t> fill(fd[f].n, 0);
+            const int64_t c0 = fd[f].clause_off, c1 = c0 + fd[f].c;
+            for (int64_t c = c0; c < c1; ++c)
+                for (int k = 0; k < K; ++k) {
+                    const uint16_t e = lits[(size_t)k * NC + c];
+                    const uint32_t i = e & 0x7fffu;
+                    ell[((size_t)first[i / kWave] + fill[i]++) * kWave + i % kWave] =
+                        ((uint32_t)(c - c0) << 4) | ((uint32_t)(e >> 15) << 3) | (uint32_t)k;
+                }
+        });
     }
     // Buckets: one per size class of the push family (the formulas of a class
     // share a launch whatever table layout each would fit, so the chains of
@@ -758,9 +799,9 @@ hp_status hp_plan(hp_plan_t *out, const hp_cnf *cnf, const hp_rbm *rbm, const hp
     for (int f = 0; f < F; ++f)
         for (int b = 0; b < B; ++b) work_fb[(size_t)f * B + b] = {f, b};
     HP_TRY(upload(&p->d_work_fb, work_fb, s), "upload work list (formula order)");
-    HP_TRY(upload(&p->d_lits, lits, s), "upload clause table");
-    HP_TRY(upload(&p->d_csr_ptr, csr_ptr, s), "upload occurrence offsets");
-    HP_TRY(upload(&p->d_occ, occ, s), "upload occurrences");
+    HP_TRY(upload(&p->d_ell, ell, s), "upload occurrence lists");
+    HP_TRY(upload(&p->d_ell_slice, ell_slice, s), "upload occurrence list offsets");
+    HP_TRY(upload(&p->d_ell_deg, ell_deg, s), "upload occurrence list lengths");
     // one step of zero records past the last formula's: a wave's last step of
     // a length run loads all 64 lanes' records (the lanes past the run are
     // masked), and the step's offset travels in the loads' scalar offset,
@@ -962,7 +1003,7 @@ hp_status hp_tune(hp_plan_t plan, const hp_state *st, int64_t n_sweeps, void *st
         }
         for (size_t ki = 0; ki < kinds.size() && e == hipSuccess; ++ki)
         for (int t = 64; t <= kMaxThreads && e == hipSuccess; t *= 2)
-        for (int dyn = 0; dyn < (orig.kind != kBucketPull && p->precision != HP_MIXED_BF16 ? 2 : 1) &&
+        for (int dyn = 0; dyn < (p->precision != HP_MIXED_BF16 ? 2 : 1) &&
                           e == hipSuccess; ++dyn) {
             bk = orig;
             bk.threads = t;

@@ -26,7 +26,7 @@ struct FormulaDev {
     int32_t c;            // C_f
     int64_t var_off;      // var_offset[f]: state block starts at var_off * B
     int64_t clause_off;   // clause_offset[f]: first clause record / column
-    int64_t ptr_off;      // var_off + f: first of the N_f+1 occurrence offsets
+    int64_t slice_off;    // pull: first of the formula's slice offsets (one more than its 64-variable slices)
     int32_t lofs[8];      // push records (sorted by length) of length <= k, k = 0..7
 };
 
@@ -133,9 +133,12 @@ template <typename Real>
 struct SweepParams {
     const FormulaDev *fd;
     const WorkItem *work;
-    const uint16_t *lits;        // pull: [K][ctot] var index (15 bits) | negated << 15
-    const uint32_t *csr_ptr;     // pull: per formula N_f+1 absolute offsets into occ
-    const uint32_t *occ;         // pull: (c_local << 4) | (negated << 3) | k, (c, k) ascending
+    // pull: occurrence lists of 64 consecutive variables (a slice) interleaved,
+    // [slice entry][64] words (c_local << 4) | (negated << 3) | k in ascending
+    // (c, k), padded with zeros to a multiple of 4 entries; slice offsets (in
+    // entries, from FormulaDev::slice_off) and the variables' list lengths
+    // ([slice][64], from 64 slice_off)
+    const uint32_t *ell, *ell_slice, *ell_deg;
     const uint4 *rec;            // push: clause records [ctot]
     const uint32_t *orig;        // push: first Philox block of the record's hidden draw [ctot]
     const int32_t *negcnt;       // push: negated slots per variable [sum N]
@@ -150,7 +153,6 @@ struct SweepParams {
     int32_t *s_max;
     uint8_t *best;
     const int64_t *t_ptr;
-    int64_t ctot;
     int64_t n_sweeps;
     Real alpha;
     double fx_scale;             // 2^-S
@@ -235,7 +237,7 @@ struct Plan {
     int32_t precision = HP_FP64;
     double alpha = 0.0;
     uint64_t seed = 0;
-    int64_t total_vars = 0, total_clauses = 0, total_occ = 0;
+    int64_t total_vars = 0, total_clauses = 0;
     int32_t max_n = 0, max_c = 0;
     int32_t threads = 0;         // workgroup size override (0 = per bucket)
     int32_t fx_shift = 0;        // S of the fixed-point accumulators
@@ -270,9 +272,9 @@ struct Plan {
     unsigned char *d_mg_nu = nullptr;
     ClauseTile *d_ctile = nullptr;        // [n_ctiles] clause tiles of all formulas, in order
     int32_t n_ctiles = 0;
-    uint16_t *d_lits = nullptr;
-    uint32_t *d_csr_ptr = nullptr;
-    uint32_t *d_occ = nullptr;
+    uint32_t *d_ell = nullptr;            // pull formulas: occurrence lists by slices,
+    uint32_t *d_ell_slice = nullptr;      //   slice offsets,
+    uint32_t *d_ell_deg = nullptr;        //   list lengths
     uint4 *d_rec = nullptr;
     uint32_t *d_orig = nullptr;
     int32_t *d_negcnt = nullptr;

@@ -20,7 +20,7 @@
 //       (clause, position) order in floating point.
 //
 // Per sweep (the round of Sec. 3.2 / appendix program, in its order), pull:
-//   clause phase  -- for each clause: gather its K inputs from LDS, form the
+//   clause phase  -- for each clause: gather its inputs from LDS, form the
 //                    literal-truth pattern m (bit k set iff literal k is true),
 //                    count m != 0, then draw its L hidden units against the
 //                    integer thresholds thr[m][l] (eqs. 2, 4, 6) and store the
@@ -201,8 +201,14 @@ __device__ __forceinline__ int wave_sum(int x) {
     return __builtin_amdgcn_readlane(x, kWave - 1);
 }
 
+// pull LDS layout: thr (rows by padded pattern) | counts | G | v | hidden masks
+constexpr int kPullCntOff = kPatterns * kMaxL * 4;
+constexpr int kPullGOff = kPullCntOff + 64 * 4;
+template <typename Real>
+constexpr int kPullVOff = kPullGOff + kHidMasks * kMaxL * (int)sizeof(Real);
+
 size_t lds_bytes_pull(int max_n, int max_c, size_t real_bytes, int32_t *v_off, int32_t *hm_off) {
-    size_t off = (size_t)kPatterns * kMaxL * 4 + (size_t)kHidMasks * kMaxL * real_bytes + 64 * 4;
+    size_t off = (size_t)(real_bytes == 4 ? kPullVOff<float> : kPullVOff<double>);
     *v_off = (int32_t)off;
     off += ((size_t)max_n + 15) / 16 * 16;
     *hm_off = (int32_t)off;
@@ -302,140 +308,6 @@ __device__ __forceinline__ uint32_t hidden_mask(const uint32_t *row, uint32_t bl
     return draw_next(m, r.x, ta.x);
 }
 
-// VPT > 0: each thread owns VPT groups of 4 consecutive variables and keeps
-// their variance EMA in registers.  VPT == 0: any number of groups, EMA read
-// and written in global memory every sweep.
-template <typename Real, int VPT>
-__global__ __launch_bounds__(1024) void sweep_pull_kernel(SweepParams<Real> P) {
-    extern __shared__ __align__(16) unsigned char lds[];
-    uint32_t *s_thr = reinterpret_cast<uint32_t *>(lds);
-    Real *s_G = reinterpret_cast<Real *>(lds + kPatterns * kMaxL * 4);
-    int *s_cnt = reinterpret_cast<int *>(lds + kPatterns * kMaxL * 4 + kHidMasks * kMaxL * sizeof(Real));
-    uint8_t *s_v = lds + P.lds_v_off;
-    uint8_t *s_hm = lds + P.lds_hm_off;
-
-    const WorkItem w = P.work[blockIdx.x];
-    const FormulaDev fd = P.fd[w.f];
-    const int N = fd.n, C = fd.c;
-    const int tid = threadIdx.x, NT = blockDim.x;
-    const int tau = P.temp_of_chain[(int64_t)w.f * P.B + w.b];
-    const int64_t sbase = fd.var_off * P.B + (int64_t)w.b * N;
-    const uint16_t *__restrict__ lits = P.lits + fd.clause_off;
-    const uint32_t *__restrict__ cptr = P.csr_ptr + fd.ptr_off;
-    const uint32_t *__restrict__ occ = P.occ;
-    const Key2 key{P.key0, P.key1 ^ (uint32_t)w.f};
-    const bool sample = P.n_sweeps > 0;
-    const int64_t S = sample ? P.n_sweeps : 1;
-    const uint32_t nbh = (uint32_t)(P.L + 3) >> 2;
-    const uint32_t lmask = (1u << P.L) - 1u;
-    const int K = P.K;
-    const int64_t ctot = P.ctot;
-    const Real alpha = P.alpha;
-    const Real two_m24 = Real(1.0 / 16777216.0);
-
-    for (int i = tid; i < kPatterns * kMaxL; i += NT) s_thr[i] = P.thr[tau * kPatterns * kMaxL + i];
-    for (int i = tid; i < kHidMasks * kMaxL; i += NT) s_G[i] = P.G[tau * kHidMasks * kMaxL + i];
-    for (int i = tid; i < N; i += NT) s_v[i] = P.v[sbase + i];
-    constexpr int VR = VPT > 0 ? VPT : 1;
-    Real nu[VR][4];
-    if (VPT > 0) {
-#pragma unroll
-        for (int j = 0; j < VR; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int i = (tid + j * NT) * 4 + q;
-                nu[j][q] = i < N ? P.nu[sbase + i] : Real(0);
-            }
-    }
-    int smax = P.s_max[(int64_t)w.f * P.B + w.b];
-    const int64_t t0 = *P.t_ptr;
-    __syncthreads();
-
-    for (int64_t s = 0; s < S; ++s) {
-        const uint64_t t = (uint64_t)(t0 + s);
-        const PhiloxSweep ps = philox_sweep_consts((uint32_t)t, (uint32_t)w.b, (uint32_t)(t >> 32), key);
-        // ---- clause phase: gather, count, hidden draw ----
-        int cnt = 0;
-        for (int c = tid; c < C; c += NT) {
-            uint32_t m = 0;
-#pragma unroll
-            for (int k = 0; k < kMaxK; ++k) {
-                if (k < K) {
-                    const uint32_t e = lits[(int64_t)k * ctot + c];
-                    m |= (uint32_t)(s_v[e & 0x7fffu] ^ (e >> 15)) << k;
-                }
-            }
-            cnt += (m != 0u);
-            if (sample) {
-                uint32_t n = hidden_mask(s_thr + m * kMaxL, (uint32_t)c * nbh, ps, key, nbh) & lmask;
-                s_hm[c] = (uint8_t)n;
-            }
-        }
-        cnt = wave_sum(cnt);
-        if ((tid & (kWave - 1)) == 0) s_cnt[tid / kWave] = cnt;
-        __syncthreads();
-        int total = 0;
-        for (int wv = 0; wv < NT / kWave; ++wv) total += s_cnt[wv];
-        const bool improved = total > smax;
-        if (improved) smax = total;
-        // ---- visible phase: scatter-add (pull), sigmoid, EMA, draw ----
-        const int groups = (N + 3) >> 2;
-        const int jmax = VPT > 0 ? VPT : (groups + NT - 1) / NT;
-#pragma unroll
-        for (int j = 0; j < (VPT > 0 ? VPT : 1); ++j) {
-          for (int jj = (VPT > 0 ? j : 0); jj < (VPT > 0 ? j + 1 : jmax); ++jj) {
-            const int grp = tid + jj * NT;
-            if (grp < groups) {
-                uint4 r = make_uint4(0, 0, 0, 0);
-                if (sample) r = philox_sweep(kPhaseVisible | (uint32_t)grp, ps, key);
-                const uint32_t rw[4] = {r.x, r.y, r.z, r.w};
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int i = grp * 4 + q;
-                    if (i < N) {
-                        const uint8_t old = s_v[i];
-                        if (improved) P.best[sbase + i] = old;
-                        if (sample) {
-                            Real x = Real(0);
-                            const uint32_t o1 = cptr[i + 1];
-                            for (uint32_t o = cptr[i]; o < o1; ++o) {
-                                const uint32_t e = occ[o];
-                                const Real g = s_G[(uint32_t)s_hm[e >> 4] * kMaxL + (e & 7u)];
-                                x += (e & 8u) ? -g : g;
-                            }
-                            const Real rho = sigmoid(x);
-                            if (VPT > 0) {
-                                nu[j][q] = ema(nu[j][q], rho, alpha);
-                            } else {
-                                P.nu[sbase + i] = ema(P.nu[sbase + i], rho, alpha);
-                            }
-                            s_v[i] = (Real(rw[q] >> 8) * two_m24) < rho ? 1 : 0;
-                        }
-                    }
-                }
-            }
-          }
-        }
-        __syncthreads();
-    }
-    for (int i = tid; i < N; i += NT) P.v[sbase + i] = s_v[i];
-    if (VPT > 0) {
-#pragma unroll
-        for (int j = 0; j < VR; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int i = (tid + j * NT) * 4 + q;
-                if (i < N) P.nu[sbase + i] = nu[j][q];
-            }
-    }
-    if (tid == 0) P.s_max[(int64_t)w.f * P.B + w.b] = smax;
-}
-
-// literal truth of a 16-bit clause slot: v[index] xor negated
-__device__ __forceinline__ uint32_t lit_of(const uint8_t *s_v, uint32_t e) {
-    return (uint32_t)s_v[e & 0x7fffu] ^ (e >> 15);
-}
-
 // Add pol * g to the accumulator of variable i; sm = 0 for a positive slot,
 // all ones for a negated one, which adds ~g = -g - 1.  The missing +1 of every
 // negated slot of a variable is a constant of the formula (negcnt) that seeds
@@ -488,6 +360,7 @@ struct PushLds {
     int64_t *x;
     uint8_t *v;
     __amdgpu_buffer_rsrc_t grs;
+    uint8_t *hm;                 // pull: the clauses' hidden masks
 };
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t table_rows(const int64_t *gtab, int tau) {
@@ -518,6 +391,13 @@ __device__ __forceinline__ PushLds push_lds_mid(unsigned char *lds, int x_off, c
     return PushLds{reinterpret_cast<uint32_t *>(lds_at(0)), reinterpret_cast<int64_t *>(lds_at(kMidGfxOff)),
                    nullptr, reinterpret_cast<int *>(lds + kMidCntOff), reinterpret_cast<int64_t *>(lds + x_off),
                    lds_at(kMidVOff), table_rows(gtab, tau)};
+}
+
+template <typename Real>
+__device__ __forceinline__ PushLds pull_lds(unsigned char *lds, int hm_off) {
+    return PushLds{reinterpret_cast<uint32_t *>(lds_at(0)), nullptr, nullptr,
+                   reinterpret_cast<int *>(lds + kPullCntOff), nullptr, lds_at(kPullVOff<Real>), no_rows(),
+                   lds + hm_off};
 }
 
 template <int kTab>
@@ -657,12 +537,17 @@ __device__ __forceinline__ void clause_one(const PushLds &L, const uint4 &r, uin
     // pattern's; for LEN < 7 the record's last word is the negation bits |
     // 2^LEN, so one XOR makes the row itself (a clause is satisfied iff its
     // row is not 2^LEN).
-    constexpr bool kRow = !kClust && LEN < 7;
-    const uint32_t m = kClust  ? pattern_fixed<LEN, kClust>(L.v, r, full)
+    // pull: the padded pattern of the table's width.
+    constexpr bool kPull = kTab == kBucketPull;
+    constexpr bool kRow = !kClust && !kPull && LEN < 7;
+    const uint32_t m = kClust || kPull ? pattern_fixed<LEN, kClust>(L.v, r, full)
                        : kRow ? gather_fixed<LEN>(L.v, r) ^ r.w
                               : gather_fixed<LEN>(L.v, r) ^ neg_bits<LEN>(r);
     count_satisfied<kRow ? (1u << LEN) : 0u>(cnt, m);
-    if (kSample) {
+    if (kSample && kPull) {
+        static_assert(!kPull || NB > 0, "the clause's index is its first block over NB");
+        L.hm[oc / (uint32_t)(NB > 0 ? NB : 1)] = (uint8_t)(hidden_mask<NB>(L.thr + m * kMaxL, oc, ps, key, 0u) & lmask);
+    } else if (kSample) {
         int64_t g[8];
         if (kClust) {
             constexpr uint32_t Kc = LEN < 3 ? 3u : (uint32_t)LEN;
@@ -747,6 +632,7 @@ __device__ __forceinline__ int first_step(const StepCounter &sc) { return sc.dyn
 template <int kTab, bool kClust>
 constexpr int step_counter_addr() {
     return (kClust ? kClustCntOff
+                   : kTab == kBucketPull ? kPullCntOff
                    : kTab == kBucketWide ? kWideCntOff : kTab == kBucketMid ? kMidCntOff : kPushCntOff) + 62 * 4;
 }
 
@@ -1386,6 +1272,152 @@ __global__ __launch_bounds__(1024) void sweep_push_kernel(SweepParams<Real> P, W
 }
 
 // --------------------------------------------------------------------------
+// Pull kernel
+// --------------------------------------------------------------------------
+// One chain per workgroup.  The clause phase walks the push kernels' records
+// (sorted by length, loaded ahead) and leaves every clause's hidden mask in
+// LDS; in the visible phase a thread takes one variable at a time, so a wave
+// reads its 64 variables' occurrence lists 64 consecutive words a time (the
+// lists of 64 variables are interleaved, padded to the longest of them), four
+// ahead of their use.  The sum runs in list order, one addition per occurrence.
+// Bound by the issue and the latency of the LDS gathers of masks and
+// contributions: 18 500 variables x 64 chains, FP64, 842 -> 254 us a sweep (a
+// thread walked four variables' lists of 4-byte words 168 bytes apart, and the
+// clause phase read K 16-bit columns per clause and always drew K literals).
+// VPT > 0: up to VPT variables per thread, their variance EMA in registers;
+// 0: any number, the EMA in global memory.
+template <typename Real, int VPT, bool kSample, int NB>
+__device__ __forceinline__ void pull_sweeps(const SweepParams<Real> &P, const PushCtx<Real> &c, const Real *s_G,
+                                            const uint32_t *__restrict__ ell, const uint32_t *__restrict__ slice,
+                                            const uint32_t *__restrict__ deg, Real (&nu)[VPT > 0 ? VPT : 1],
+                                            int &smax) {
+    const PushLds &L = c.L;
+    const int N = c.N, tid = c.tid, NT = c.NT, lane = tid & (kWave - 1);
+    const Real two_m24 = Real(1.0 / 16777216.0);
+    const RecView rv = rec_view(c.rec, c.orig, c.C);
+    auto step_counter = [&](int64_t s) { return StepCounter{(int)s * c.steps, c.dyn, c.wave, NT / kWave}; };
+    StepPipe pipe = start_pipe(rv, c.lofs, step_counter(0), lane);
+    const int jmax = VPT > 0 ? VPT : (N + NT - 1) / NT;
+    for (int64_t s = 0; s < c.S; ++s) {
+        const uint64_t t = (uint64_t)(c.t0 + s);
+        const PhiloxSweep ps = philox_sweep_consts((uint32_t)t, (uint32_t)c.b, (uint32_t)(t >> 32), c.key);
+        const int cnt = clause_phase<kSample, false, NB, kBucketPull>(L, rv, c.lofs, pipe, step_counter(s), lane, ps,
+                                                                      c.key, c.nbh, c.full, c.lmask);
+        const int total = block_total(L, cnt, tid, s);
+        const bool improved = total > smax;
+        if (improved) smax = total;
+#pragma unroll
+        for (int jv = 0; jv < (VPT > 0 ? VPT : 1); ++jv)
+            for (int jj = (VPT > 0 ? jv : 0); jj < (VPT > 0 ? jv + 1 : jmax); ++jj) {
+                const int i = tid + jj * NT;
+                if ((i & ~(kWave - 1)) >= N) break;                      // the whole wave is past the end
+                const bool act = i < N;
+                if (improved && act) P.best[c.sbase + i] = L.v[i];
+                if (!kSample) continue;
+                const int sl = c.wave + jj * (NT / kWave);
+                const uint32_t e0 = slice[sl];
+                const int width = (int)(slice[sl + 1] - e0);             // a multiple of 4
+                const uint32_t *__restrict__ row = ell + (size_t)e0 * kWave + lane;
+                const int d = act ? (int)deg[i] : 0;
+                const uint4 r = philox_sweep(kPhaseVisible | (uint32_t)(i >> 2), ps, c.key);
+                Real x = Real(0);
+                uint32_t e[4], f[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) e[u] = row[(size_t)u * kWave];
+                for (int j = 0; j < width; j += 4) {
+                    const size_t nx = (size_t)min(j + 4, width - 4) * kWave;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) f[u] = row[nx + (size_t)u * kWave];
+                    uint32_t h[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) h[u] = L.hm[e[u] >> 4];
+                    Real g[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) g[u] = s_G[h[u] * kMaxL + (e[u] & 7u)];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (j + u < d) x += (e[u] & 8u) ? -g[u] : g[u];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) e[u] = f[u];
+                }
+                if (act) {
+                    const int q = i & 3;
+                    const uint32_t word = q == 0 ? r.x : q == 1 ? r.y : q == 2 ? r.z : r.w;
+                    const Real rho = sigmoid(x);
+                    if (VPT > 0)
+                        nu[jv] = ema(nu[jv], rho, c.alpha);
+                    else
+                        P.nu[c.sbase + i] = ema(P.nu[c.sbase + i], rho, c.alpha);
+                    L.v[i] = (Real(word >> 8) * two_m24) < rho ? 1 : 0;
+                }
+            }
+        lds_barrier();
+    }
+}
+
+template <typename Real, int VPT>
+__global__ __launch_bounds__(1024) void sweep_pull_kernel(SweepParams<Real> P) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    const WorkItem w = P.work[blockIdx.x];
+    const FormulaDev fd = P.fd[w.f];
+    const int N = fd.n;
+    const int tid = threadIdx.x, NT = blockDim.x;
+    const int tau = P.temp_of_chain[(int64_t)w.f * P.B + w.b];
+    PushCtx<Real> c;
+    c.L = pull_lds<Real>(lds, P.lds_hm_off);
+    const PushLds &L = c.L;
+    Real *s_G = reinterpret_cast<Real *>(lds_at(kPullGOff));
+    c.rec = P.rec + fd.clause_off;
+    c.orig = P.orig + fd.clause_off;
+    c.sbase = fd.var_off * P.B + (int64_t)w.b * N;
+    c.S = P.n_sweeps > 0 ? P.n_sweeps : 1;
+    c.t0 = *P.t_ptr;
+    c.key = Key2{P.key0, P.key1 ^ (uint32_t)w.f};
+    c.alpha = P.alpha;
+    c.N = N;
+    c.C = fd.c;
+    c.tid = tid;
+    c.NT = NT;
+    c.b = w.b;
+    c.wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    c.dyn = P.dyn_steps;
+    c.steps = sweep_step_numbers(fd.lofs);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) c.lofs[k] = fd.lofs[k];
+    c.nbh = (uint32_t)(P.L + 3) >> 2;
+    c.full = (1u << P.K) - 1u;
+    c.lmask = (1u << P.L) - 1u;
+
+    for (int i = tid; i < kPatterns * kMaxL; i += NT) L.thr[i] = P.thr[tau * kPatterns * kMaxL + i];
+    for (int i = tid; i < kHidMasks * kMaxL; i += NT) s_G[i] = P.G[tau * kHidMasks * kMaxL + i];
+    for (int i = tid; i < N; i += NT) L.v[i] = P.v[c.sbase + i];
+    constexpr int VR = VPT > 0 ? VPT : 1;
+    Real nu[VR];
+#pragma unroll
+    for (int j = 0; j < VR; ++j) nu[j] = VPT > 0 && tid + j * NT < N ? P.nu[c.sbase + tid + j * NT] : Real(0);
+    int smax = P.s_max[(int64_t)w.f * P.B + w.b];
+    if (tid == 0) L.cnt[0] = L.cnt[1] = L.cnt[62] = 0;
+    __syncthreads();
+
+    const uint32_t *slice = P.ell_slice + fd.slice_off;
+    const uint32_t *deg = P.ell_deg + fd.slice_off * kWave;
+    if (P.n_sweeps <= 0)
+        pull_sweeps<Real, VPT, false, 1>(P, c, s_G, P.ell, slice, deg, nu, smax);
+    else if (c.nbh > 1)
+        pull_sweeps<Real, VPT, true, 2>(P, c, s_G, P.ell, slice, deg, nu, smax);
+    else
+        pull_sweeps<Real, VPT, true, 1>(P, c, s_G, P.ell, slice, deg, nu, smax);
+
+    for (int i = tid; i < N; i += NT) P.v[c.sbase + i] = L.v[i];
+    if (VPT > 0) {
+#pragma unroll
+        for (int j = 0; j < VR; ++j)
+            if (tid + j * NT < N) P.nu[c.sbase + tid + j * NT] = nu[j];
+    }
+    if (tid == 0) P.s_max[(int64_t)w.f * P.B + w.b] = smax;
+}
+
+// --------------------------------------------------------------------------
 // Split kernel: G co-resident workgroups per chain
 // --------------------------------------------------------------------------
 // Exchange between the G workgroups of one chain.  Partial logits, partial
@@ -1831,11 +1863,7 @@ const void *mixed_kernel_ptr(int vpt) {
 
 template <typename Real>
 const void *pull_kernel_ptr(int vpt) {
-    switch (vpt) {
-        case 1: return (const void *)sweep_pull_kernel<Real, 1>;
-        case 2: return (const void *)sweep_pull_kernel<Real, 2>;
-        default: return (const void *)sweep_pull_kernel<Real, 0>;
-    }
+    return vpt > 0 ? (const void *)sweep_pull_kernel<Real, 4> : (const void *)sweep_pull_kernel<Real, 0>;
 }
 
 template <typename Real>
@@ -1912,9 +1940,9 @@ SweepParams<Real> sweep_params(const Plan &p, const hp_state &st, int64_t n_swee
     SweepParams<Real> P;
     P.fd = p.d_fd;
     P.work = p.d_work;
-    P.lits = p.d_lits;
-    P.csr_ptr = p.d_csr_ptr;
-    P.occ = p.d_occ;
+    P.ell = p.d_ell;
+    P.ell_slice = p.d_ell_slice;
+    P.ell_deg = p.d_ell_deg;
     P.rec = p.d_rec;
     P.orig = p.d_orig;
     P.negcnt = p.d_negcnt;
@@ -1931,7 +1959,6 @@ SweepParams<Real> sweep_params(const Plan &p, const hp_state &st, int64_t n_swee
     P.s_max = st.s_max;
     P.best = st.best;
     P.t_ptr = st.t;
-    P.ctot = p.total_clauses;
     P.n_sweeps = n_sweeps;
     P.alpha = (Real)p.alpha;
     P.key0 = (uint32_t)(p.seed & 0xffffffffu);

@@ -36,3 +36,35 @@ def test_small_formulas_on_many_threads(hip, n, k, chains, threads, precision):
         compare_state(st.formula(0), (ost.v, ost.nu, ost.s_max, ost.best), "f64", f"n={n}",
                       f64_bounds(plan, [T])[1])
     plan.free()
+
+
+# pull: slices of 64 variables and their edges, more than four variables per
+# thread (averages in global memory), one Philox block per clause, and a variable
+# that sits in most clauses (its slice's lists padded to its length)
+@pytest.mark.parametrize("n,k,threads,hub,precision", [
+    (63, 7, 64, False, "f64"), (65, 7, 64, False, "f32"), (300, 7, 64, False, "f64"), (257, 3, 64, False, "f32"),
+    (513, 7, 256, True, "f64"), (130, 3, 128, True, "f32")])
+def test_pull_slices(hip, n, k, threads, hub, precision):
+    T = wl.random_formula(n, 52, k=k, lengths=[1, 2, 3] if k == 3 else wl.LENGTHS,
+                          probs=[0.2, 0.5, 0.3] if k == 3 else wl.LENGTH_PROBS)
+    if hub:
+        T[:, ::2] = np.where(T[:, ::2] == T[:1, ::2], np.sign(T[:1, ::2]) * (n - 1), T[:, ::2])
+    W, b, _ = wl.pretrained_rbm(k, wl.FSTAR_PAIR)
+    chains = 3
+    temps = wl.default_temperatures(chains, 2)
+    v0 = wl.initial_state(chains, n, 52)
+    plan = hp.Plan([T], [n], W, b, chains=chains, temps=temps, precision=precision, seed=52, threads=threads,
+                   kernel="pull")
+    st = plan.new_state([v0])
+    op, ost = R.plan(T, n, W, b), R.initial(v0)
+    say(f"[pull] n={n} k={k} threads={threads} hub={hub} {precision}")
+    if precision == "f32":
+        for _ in range(4):
+            teacher_forced_sweep(plan, st, 0, ost, op, temps, alpha=1e-3, seed=52, prec="f32")
+    else:
+        for S in (4, 0, 6):
+            plan.run(st, S)
+            if S:
+                ost = R.run(ost, op, temps, S, alpha=1e-3, seed=52)
+        compare_state(st.formula(0), (ost.v, ost.nu, ost.s_max, ost.best), "f64", f"n={n}", 1e-13)
+    plan.free()
