@@ -153,6 +153,10 @@ struct SweepParams {
     int32_t *s_max;
     uint8_t *best;
     const int64_t *t_ptr;
+    // (the eight bytes keep the loads of the arguments below small: without
+    // them, or with alpha aligned to 16, the compiler fetches 16 words at once
+    // and the FP64 sweep kernels spill them, 3% on the split launch)
+    int64_t pad;
     int64_t n_sweeps;
     Real alpha;
     double fx_scale;             // 2^-S
@@ -302,6 +306,9 @@ struct RunBuffers {
     int64_t *xpart;              // split: [items][G][nstride] partial logits
     uint8_t *vbuf;               // split: [items][nstride] packed new values
     int32_t *cnt;                // split: [items][2][kMaxSplit] partial counts
+    // the sweep counter at the run's start (in the first counter line, beside
+    // the counter itself)
+    int64_t *t0() const { return reinterpret_cast<int64_t *>(queue + 16); }
 };
 constexpr size_t kScratchBytes = size_t(16) << 20;
 RunBuffers plan_buffers(const Plan &p);
@@ -318,8 +325,6 @@ void *static_scratch(int device);
 hipError_t launch_tables(const Plan &p, hipStream_t s);
 hipError_t launch_sweep(const Plan &p, const hp_state &st, int64_t n_sweeps, hipStream_t s);
 hipError_t launch_sweep(const Plan &p, const hp_state &st, int64_t n_sweeps, hipStream_t s, const RunBuffers &rb);
-// the launches of a run without the sweep-counter advance
-hipError_t launch_buckets(const Plan &p, const hp_state &st, int64_t n_sweeps, hipStream_t s, const RunBuffers &rb);
 // one bucket alone (no fork/join, no counter advance): used by the tuner
 hipError_t launch_bucket(const Plan &p, const Bucket &b, const hp_state &st, int64_t n_sweeps, hipStream_t s);
 // raise the dynamic-LDS limit of every sweep kernel to `bytes` (once per plan)
