@@ -26,6 +26,8 @@ constexpr int kOffW1 = 0, kOffB1 = kF * kH, kOffW2 = kOffB1 + kH, kOffB2 = kOffW
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
+typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
 
 __device__ __forceinline__ uint16_t bf16_bits(float x) {
     const __bf16 b = (__bf16)x;   // round to nearest even
@@ -124,27 +126,51 @@ __global__ __launch_bounds__(kFeatThreads) void feature_kernel(const uint4 *__re
     }
 }
 
-// ---- perceptron: forward -------------------------------------------------------
-// One wave per 32-row tile (waves stride over the tiles).  Hidden layer on
-// MFMA 32x32x16 bf16: lane l holds rows/columns as
-//   A[32 x 16]: row l%32, k = (l/32)*8 + 0..7;  B[16 x 32]: column l%32, same k;
-//   D[32 x 32]: register i -> row (i/4)*8 + (l/32)*4 + i%4, column l%32.
-constexpr int kWaves = 4;
+// ---- perceptron ---------------------------------------------------------------
+// Hidden layer on MFMA 32x32x16 bf16.  Lane l supplies index l%32 of an operand
+// (a row of A, a column of B) with k = (l/32)*8 + 0..7, the same registers for
+// either side; D[32 x 32]: register i -> row (i/4)*8 + (l/32)*4 + i%4, column
+// l%32.  The waves of a workgroup split the 256 hidden units in chunks of 32,
+// and a wave keeps its chunks' weights, biases and output weights in registers
+// for the whole launch.  With the weights as A and a tile of 32 data rows as B,
+// a lane holds 16 hidden units of one data row: the output dot product is a
+// maximum and a multiply-add per unit with no sum across lanes (the bias enters
+// as the product's C operand), then one add between the wave's halves and one
+// sum over the waves in LDS.
+constexpr int kStepRows = 128;   // data rows per workgroup step: 4 tiles
 
 // row of D register i for lane half h (see above)
 __device__ __forceinline__ int d_row(int i, int h) { return (i / 4) * 8 + h * 4 + (i % 4); }
 
-// W1 (transposed bfloat16), b1 and w2 of the network into LDS
-__device__ __forceinline__ void load_weights(const float *params, const uint16_t *wbf, uint16_t *s_w1t, float *s_b1,
-                                             float *s_w2, int tid) {
-    for (int i = tid; i < kH * kF; i += kWaves * 64) s_w1t[i] = wbf[i];
-    for (int i = tid; i < kH; i += kWaves * 64) {
-        s_b1[i] = params[kOffB1 + i];
-        s_w2[i] = bf16_value(wbf[kH * kF + i]);
+// one hidden chunk's constants: weights (both k-steps; lane l%32 = unit), and
+// bias and output weight of the units in the lane's D registers
+struct HiddenChunk {
+    bf16x8 w0, w1;
+    f32x16 b1, w2;
+};
+
+__device__ __forceinline__ HiddenChunk load_chunk(const float *params, const uint16_t *wbf, int j, int lane) {
+    const int half = lane >> 5;
+    const uint16_t *w = wbf + (j * 32 + (lane & 31)) * kF + half * 8;
+    HiddenChunk c;
+    // element-wise: the caller's buffers are aligned to their elements only
+    uint32_t a[4], b[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        a[m] = (uint32_t)w[2 * m] | ((uint32_t)w[2 * m + 1] << 16);
+        b[m] = (uint32_t)w[16 + 2 * m] | ((uint32_t)w[16 + 2 * m + 1] << 16);
     }
+    c.w0 = __builtin_bit_cast(bf16x8, make_uint4(a[0], a[1], a[2], a[3]));
+    c.w1 = __builtin_bit_cast(bf16x8, make_uint4(b[0], b[1], b[2], b[3]));
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        c.b1[i] = params[kOffB1 + j * 32 + d_row(i, half)];
+        c.w2[i] = bf16_value(wbf[kH * kF + j * 32 + d_row(i, half)]);
+    }
+    return c;
 }
 
-// The two A operands (k-steps) of the 32-row tile starting at row0: lane l
+// The two operands (k-steps) of the 32-row tile starting at row0: lane l
 // takes row row0 + l%32, features (l/32)*8 + 0..7 and 16 + (l/32)*8 + 0..7
 // (zeros past the last row).  Operands move as integer words: element m of a
 // bfloat16 vector is bits 16*(m%2) of word m/2.
@@ -160,126 +186,123 @@ __device__ __forceinline__ void load_x_tile(const uint16_t *x, int64_t rows, int
     }
 }
 
-// pre-activations of hidden columns [32 j, 32 j + 32) for the tile's rows
-__device__ __forceinline__ f32x16 hidden_chunk(const uint16_t *s_w1t, int j, int lane, bf16x8 a0, bf16x8 a1) {
-    const int col = j * 32 + (lane & 31), half = lane >> 5;
-    const bf16x8 bw0 = *reinterpret_cast<const bf16x8 *>(s_w1t + col * kF + half * 8);
-    const bf16x8 bw1 = *reinterpret_cast<const bf16x8 *>(s_w1t + col * kF + 16 + half * 8);
-    f32x16 acc = {};
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, bw0, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, bw1, acc, 0, 0, 0);
-    return acc;
+// w2 . relu(W1^T x + b1) of the tile's rows over the units of one chunk that
+// this half of the wave holds, in FP32; the sums of chunks, halves and waves are
+// taken in FP64 (a few additions per row, where FP32 ones would leave q 4%
+// further from the exact value than sums across the lanes do)
+__device__ __forceinline__ float chunk_logit(const HiddenChunk &c, bf16x8 x0, bf16x8 x1) {
+    f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c.w0, x0, c.b1, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c.w1, x1, acc, 0, 0, 0);
+    float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s[i & 3] = fmaf(fmaxf(acc[i], 0.0f), c.w2[i], s[i & 3]);
+    return (s[0] + s[1]) + (s[2] + s[3]);
 }
 
-// output logits w2 . relu(W1^T x + b1) of the tile's rows, without b2: after
-// the butterfly every lane of half h holds s[i] for row d_row(i, h)
-__device__ __forceinline__ void tile_logits(const uint16_t *s_w1t, const float *s_b1, const float *s_w2, int lane,
-                                            bf16x8 a0, bf16x8 a1, float (&s)[16]) {
-    for (int i = 0; i < 16; ++i) s[i] = 0.0f;
-    // not unrolled: the unrolled loop hoists every chunk's operand loads and
-    // needs twice the registers (half the resident waves) for no gain
-#pragma unroll 1
-    for (int j = 0; j < 8; ++j) {
-        const f32x16 acc = hidden_chunk(s_w1t, j, lane, a0, a1);
-        const int col = j * 32 + (lane & 31);
-        const float bb = s_b1[col], ww = s_w2[col];
-        for (int i = 0; i < 16; ++i) s[i] += fmaxf(acc[i] + bb, 0.0f) * ww;
-    }
-    for (int off = 1; off < 32; off <<= 1)
-        for (int i = 0; i < 16; ++i) s[i] += __shfl_xor(s[i], off, 64);
-}
+// Forward: 4 waves of 64 units each.  Bound by the two VALU instructions per
+// row and unit: 524 288 rows take 25 us, 4 M rows 175 us (393 TFLOP/s of
+// products), before 39 and 264 us with rows as A, whose dot product needed a
+// five-step sum across the lanes for every row.
+constexpr int kFwdWaves = 4;
 
-__global__ __launch_bounds__(kWaves * 64) void mlp_forward_kernel(const uint16_t *__restrict__ x, int64_t rows,
-                                                                  const float *__restrict__ params,
-                                                                  const uint16_t *__restrict__ wbf,
-                                                                  float *__restrict__ q_out) {
-    __shared__ __align__(16) uint16_t s_w1t[kH * kF];          // W1 transposed: [column][feature]
-    __shared__ float s_b1[kH], s_w2[kH];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    load_weights(params, wbf, s_w1t, s_b1, s_w2, tid);
-    __syncthreads();
+__global__ __launch_bounds__(kFwdWaves *kWave) void mlp_forward_kernel(const uint16_t *__restrict__ x, int64_t rows,
+                                                                       const float *__restrict__ params,
+                                                                       const uint16_t *__restrict__ wbf,
+                                                                       float *__restrict__ q_out) {
+    __shared__ double s_part[2][kFwdWaves][kStepRows];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const HiddenChunk c0 = load_chunk(params, wbf, 2 * wave, lane), c1 = load_chunk(params, wbf, 2 * wave + 1, lane);
     const float b2 = params[kOffB2];
-    const int half = lane >> 5, col_in = lane & 31;
-    const int64_t n_tiles = (rows + 31) / 32;
-    for (int64_t tile = (int64_t)blockIdx.x * kWaves + wave; tile < n_tiles; tile += (int64_t)gridDim.x * kWaves) {
-        uint4 x0, x1;
-        load_x_tile(x, rows, tile * 32, lane, x0, x1);
-        float s[16];
-        tile_logits(s_w1t, s_b1, s_w2, lane, __builtin_bit_cast(bf16x8, x0), __builtin_bit_cast(bf16x8, x1), s);
-        if (col_in == 0)
-            for (int i = 0; i < 16; ++i) {
-                const int64_t r = tile * 32 + d_row(i, half);
-                if (r < rows) q_out[r] = 1.0f / (1.0f + expf(-(s[i] + b2)));
-            }
-    }
-}
-
-// ---- perceptron: backward --------------------------------------------------------
-// A workgroup of 4 waves takes 128 rows per step, as 4 tiles of 32.
-//   pass 1: wave w computes the logits of tile w (all 256 hidden columns, as
-//           the forward kernel); lanes 0..31 then take one row each for q, the
-//           output gradient g = (q - y) / rows and the loss; tile w's rows (row
-//           major and transposed) and g go to LDS;
-//   pass 2: wave w owns hidden columns [64 w, 64 w + 64) (two MFMA column
-//           chunks): for each of the 4 tiles it recomputes their
-//           pre-activations, forms dh = g w2 relu'(pre) (bfloat16 for the
-//           product) and adds x^T dh to its dW1 chunks, g h to dw2 and dh to db1.
-// Each dW1 column is accumulated by one wave only: a wave keeps 2 chunks of
-// accumulators instead of all 8 (the register file then holds several waves
-// per SIMD), and the workgroup's row of the workspace needs a cross-wave sum
-// for b2 and the loss only.  The x^T dh product reuses the D layout as its B
-// operand by ordering the reduction index (the rows) as D does:
-// step s, k = (l/32)*8 + m  <->  row ((s*8 + m)/4)*8 + (l/32)*4 + m%4.
-// (3 waves per SIMD: the register budget of 170 holds pass 2 without spills;
-// the compiler's own choice, 2 waves, ran 8% slower)
-__global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(3))) void mlp_backward_kernel(const uint16_t *__restrict__ x,
-                                                                   const float *__restrict__ y, int64_t rows,
-                                                                   const float *__restrict__ params,
-                                                                   const uint16_t *__restrict__ wbf,
-                                                                   float *__restrict__ part) {
-    __shared__ __align__(16) uint16_t s_w1t[kH * kF];
-    __shared__ float s_b1[kH], s_w2[kH];
-    __shared__ __align__(16) uint16_t s_x[kWaves][32 * kF];   // tile rows: [row][feature]
-    __shared__ __align__(16) uint16_t s_xt[kWaves][kF * 32];  // transposed: [feature][row]
-    __shared__ __align__(16) float s_o[kWaves][32];           // logits, then g
-    __shared__ float s_red[kWaves][2];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    load_weights(params, wbf, s_w1t, s_b1, s_w2, tid);
-    __syncthreads();
-    const float b2 = params[kOffB2];
-    const float inv_rows = 1.0f / (float)rows;
-    const int half = lane >> 5, col_in = lane & 31;
-    const int64_t n_steps = (rows + 127) / 128;
-    f32x16 dw1[2] = {f32x16{}, f32x16{}};
-    float dw2[2] = {0.0f, 0.0f}, db1[2] = {0.0f, 0.0f};
-    float db2 = 0.0f, lsum = 0.0f;                // lanes 0..31: their rows' sums
-
-    for (int64_t step = blockIdx.x; step < n_steps; step += gridDim.x) {   // uniform over the workgroup
-        // ---- pass 1: tile `wave` ----
-        const int64_t row0 = (step * kWaves + wave) * 32;
-        uint4 x0, x1;
-        load_x_tile(x, rows, row0, lane, x0, x1);
-        *reinterpret_cast<uint4 *>(&s_x[wave][col_in * kF + half * 8]) = x0;
-        *reinterpret_cast<uint4 *>(&s_x[wave][col_in * kF + 16 + half * 8]) = x1;
-        {
-            const uint32_t w0[4] = {x0.x, x0.y, x0.z, x0.w}, w1[4] = {x1.x, x1.y, x1.z, x1.w};
-            for (int m = 0; m < 8; ++m) {
-                s_xt[wave][(half * 8 + m) * 32 + col_in] = (uint16_t)(w0[m >> 1] >> (16 * (m & 1)));
-                s_xt[wave][(16 + half * 8 + m) * 32 + col_in] = (uint16_t)(w1[m >> 1] >> (16 * (m & 1)));
-            }
+    const int64_t n_steps = (rows + kStepRows - 1) / kStepRows;
+    int buf = 0;
+    for (int64_t step = blockIdx.x; step < n_steps; step += gridDim.x, buf ^= 1) {   // uniform over the workgroup
+        uint4 x0[4], x1[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) load_x_tile(x, rows, step * kStepRows + 32 * t, lane, x0[t], x1[t]);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const bf16x8 a0 = __builtin_bit_cast(bf16x8, x0[t]), a1 = __builtin_bit_cast(bf16x8, x1[t]);
+            double s = (double)chunk_logit(c0, a0, a1) + (double)chunk_logit(c1, a0, a1);
+            s += __shfl_xor(s, 32, kWave);
+            if (lane < 32) s_part[buf][wave][32 * t + lane] = s;
         }
-        float s[16];
-        tile_logits(s_w1t, s_b1, s_w2, lane, __builtin_bit_cast(bf16x8, x0), __builtin_bit_cast(bf16x8, x1), s);
-        if (col_in == 0)
-            for (int q4 = 0; q4 < 4; ++q4)
-                *reinterpret_cast<float4 *>(&s_o[wave][q4 * 8 + half * 4]) =
-                    make_float4(s[4 * q4] + b2, s[4 * q4 + 1] + b2, s[4 * q4 + 2] + b2, s[4 * q4 + 3] + b2);
+        __syncthreads();          // (the other buffer's readers passed it before writing here again)
+        const int64_t r = step * kStepRows + tid;
+        if (tid < kStepRows && r < rows) {
+            const float o = (float)(((s_part[buf][0][tid] + s_part[buf][1][tid]) +
+                                     (s_part[buf][2][tid] + s_part[buf][3][tid])) + (double)b2);
+            q_out[r] = 1.0f / (1.0f + expf(-o));
+        }
+    }
+}
+
+// Backward: 8 waves of 32 units each, 128 rows per step.
+//   pass 1: logits as in the forward kernel; 128 threads then take one row each
+//           for q, the output gradient g = (q - y) / rows and the loss; the
+//           rows, and the rows transposed, go to LDS on the way;
+//   pass 2: with the rows as A and the wave's weights as B, a lane holds 16 rows
+//           of its unit: dh = g w2 relu'(pre) (bfloat16 for the product) adds
+//           x^T dh to the wave's dW1 chunk, g h to dw2 and dh to db1.
+// The x^T dh product reuses the D layout as its B operand by ordering the
+// reduction index (the rows) as D does:
+// step s, k = (l/32)*8 + m  <->  row ((s*8 + m)/4)*8 + (l/32)*4 + m%4.
+// Each dW1 column is summed by one wave only; a workgroup writes its sums to a
+// row of the workspace, and half as many rows as before (512) halve what the
+// reduction below moves.  262 144 rows: 38 us and 5.3 us for the reduction,
+// before 77.7 and 21.1 (every wave computed the logits of its own tile with the
+// weights read from LDS, and summed them across the lanes).
+constexpr int kBwdWaves = 8;
+constexpr int kMaxParts = 512;
+constexpr int kXStride = 40;      // halves per staged row: 16-byte aligned, off the banks' period
+constexpr int kXtStride = 36;     // halves per staged feature: 8-byte aligned
+
+__global__ __launch_bounds__(kBwdWaves *kWave) __attribute__((amdgpu_waves_per_eu(4))) void mlp_backward_kernel(
+    const uint16_t *__restrict__ x, const float *__restrict__ y, int64_t rows, const float *__restrict__ params,
+    const uint16_t *__restrict__ wbf, float *__restrict__ part) {
+    __shared__ __align__(16) uint16_t s_x[2][4][32 * kXStride];       // tile rows: [row][feature]
+    __shared__ __align__(16) uint16_t s_xt[2][4][kF * kXtStride];     // transposed: [feature][row]
+    __shared__ double s_part[kBwdWaves][kStepRows];
+    __shared__ __align__(16) float s_g[kStepRows];
+    __shared__ float s_red[2][2];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int half = lane >> 5, col_in = lane & 31, col = wave * 32 + col_in;
+    const HiddenChunk c = load_chunk(params, wbf, wave, lane);
+    const float b2 = params[kOffB2], bb = params[kOffB1 + col], ww = bf16_value(wbf[kH * kF + col]);
+    const float inv_rows = 1.0f / (float)rows;
+    const int64_t n_steps = (rows + kStepRows - 1) / kStepRows;
+    f32x16 dw1 = {};
+    float dw2 = 0.0f, db1 = 0.0f, db2 = 0.0f, lsum = 0.0f;      // db2, lsum: threads 0..127, their rows' sums
+    int buf = 0;
+    for (int64_t step = blockIdx.x; step < n_steps; step += gridDim.x, buf ^= 1) {   // uniform over the workgroup
+        // ---- pass 1 ----
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            uint4 x0, x1;
+            load_x_tile(x, rows, step * kStepRows + 32 * t, lane, x0, x1);
+            // waves 2t and 2t + 1 stage tile t: its features' first and second 16
+            if ((wave >> 1) == t) {
+                const uint4 v = (wave & 1) ? x1 : x0;
+                const int f0 = (wave & 1) * 16 + half * 8;
+                *reinterpret_cast<uint4 *>(&s_x[buf][t][col_in * kXStride + f0]) = v;
+                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (int m = 0; m < 8; ++m)
+                    s_xt[buf][t][(f0 + m) * kXtStride + col_in] = (uint16_t)(w[m >> 1] >> (16 * (m & 1)));
+            }
+            double s = (double)chunk_logit(c, __builtin_bit_cast(bf16x8, x0), __builtin_bit_cast(bf16x8, x1));
+            s += __shfl_xor(s, 32, kWave);
+            if (lane < 32) s_part[wave][32 * t + lane] = s;
+        }
         __syncthreads();
-        if (lane < 32) {
-            const int64_t r = row0 + lane;
+        if (tid < kStepRows) {
+            const int64_t r = step * kStepRows + tid;
             float g = 0.0f;
             if (r < rows) {
-                const float o = s_o[wave][lane], yy = y[r];
+                double p[kBwdWaves / 2];
+#pragma unroll
+                for (int w = 0; w < kBwdWaves / 2; ++w) p[w] = s_part[2 * w][tid] + s_part[2 * w + 1][tid];
+                const float o = (float)(((p[0] + p[1]) + (p[2] + p[3])) + (double)b2);
+                const float yy = y[r];
                 const float qq = 1.0f / (1.0f + expf(-o));
                 g = (qq - yy) * inv_rows;
                 // softplus(o) - y o
@@ -287,81 +310,76 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(3))
                 lsum += sp - yy * o;
                 db2 += g;
             }
-            s_o[wave][lane] = g;
+            s_g[tid] = g;
         }
         __syncthreads();
-        // ---- pass 2: columns of chunks 2 wave, 2 wave + 1 over the 4 tiles ----
-        for (int t = 0; t < kWaves; ++t) {
-            const bf16x8 a0 = *reinterpret_cast<const bf16x8 *>(&s_x[t][col_in * kF + half * 8]);
-            const bf16x8 a1 = *reinterpret_cast<const bf16x8 *>(&s_x[t][col_in * kF + 16 + half * 8]);
-            uint32_t t0[4], t1[4];   // x^T with rows in the D-register order
-            for (int m = 0; m < 8; m += 2) {
-                const int r0 = d_row(m, half), r1 = d_row(8 + m, half);
-                t0[m >> 1] = *reinterpret_cast<const uint32_t *>(&s_xt[t][col_in * 32 + r0]);
-                t1[m >> 1] = *reinterpret_cast<const uint32_t *>(&s_xt[t][col_in * 32 + r1]);
-            }
-            const bf16x8 ax0 = __builtin_bit_cast(bf16x8, make_uint4(t0[0], t0[1], t0[2], t0[3]));
-            const bf16x8 ax1 = __builtin_bit_cast(bf16x8, make_uint4(t1[0], t1[1], t1[2], t1[3]));
-            float g[16];
+        // ---- pass 2: the wave's units over the 4 tiles (the next step's
+        // pass 1 stages into the other buffers) ----
+#pragma unroll 1
+        for (int t = 0; t < 4; ++t) {
+            const uint16_t *xr = &s_x[buf][t][col_in * kXStride + half * 8];
+            const bf16x8 a0 = *reinterpret_cast<const bf16x8 *>(xr);
+            const bf16x8 a1 = *reinterpret_cast<const bf16x8 *>(xr + 16);
+            // x^T with rows in the D-register order: 4 consecutive rows a read
+            const uint16_t *xt = &s_xt[buf][t][col_in * kXtStride + half * 4];
+            uint2 p[4];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) p[m] = *reinterpret_cast<const uint2 *>(xt + 8 * m);
+            const bf16x8 ax0 = __builtin_bit_cast(bf16x8, make_uint4(p[0].x, p[0].y, p[1].x, p[1].y));
+            const bf16x8 ax1 = __builtin_bit_cast(bf16x8, make_uint4(p[2].x, p[2].y, p[3].x, p[3].y));
+            f32x16 acc = {};
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, c.w0, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, c.w1, acc, 0, 0, 0);
+            uint32_t dq[8];
+#pragma unroll
             for (int q4 = 0; q4 < 4; ++q4) {
-                const float4 v = *reinterpret_cast<const float4 *>(&s_o[t][q4 * 8 + half * 4]);
-                g[4 * q4] = v.x;
-                g[4 * q4 + 1] = v.y;
-                g[4 * q4 + 2] = v.z;
-                g[4 * q4 + 3] = v.w;
-            }
-            for (int c = 0; c < 2; ++c) {
-                const int j = 2 * wave + c, col = j * 32 + col_in;
-                const f32x16 acc = hidden_chunk(s_w1t, j, lane, a0, a1);
-                const float bb = s_b1[col], ww = s_w2[col];
-                uint32_t dq[8];
-                for (int i = 0; i < 16; ++i) {
-                    const float pre = acc[i] + bb;
-                    dw2[c] += g[i] * fmaxf(pre, 0.0f);
-                    const float dh = pre > 0.0f ? g[i] * ww : 0.0f;
-                    db1[c] += dh;
-                    const uint32_t bits = bf16_bits(dh);
-                    dq[i >> 1] = (i & 1) ? (dq[i >> 1] | (bits << 16)) : bits;
+                const float4 g4 = *reinterpret_cast<const float4 *>(&s_g[32 * t + q4 * 8 + half * 4]);
+                const float g[4] = {g4.x, g4.y, g4.z, g4.w};
+                float dh[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const float pre = acc[4 * q4 + k] + bb;
+                    dw2 = fmaf(g[k], fmaxf(pre, 0.0f), dw2);
+                    dh[k] = pre > 0.0f ? g[k] * ww : 0.0f;
+                    db1 += dh[k];
                 }
-                const bf16x8 d0 = __builtin_bit_cast(bf16x8, make_uint4(dq[0], dq[1], dq[2], dq[3]));
-                const bf16x8 d1 = __builtin_bit_cast(bf16x8, make_uint4(dq[4], dq[5], dq[6], dq[7]));
-                dw1[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ax0, d0, dw1[c], 0, 0, 0);
-                dw1[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ax1, d1, dw1[c], 0, 0, 0);
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+                    dq[2 * q4 + k] = __builtin_bit_cast(
+                        uint32_t, __builtin_convertvector((f32x2){dh[2 * k], dh[2 * k + 1]}, bf16x2));
             }
+            const bf16x8 d0 = __builtin_bit_cast(bf16x8, make_uint4(dq[0], dq[1], dq[2], dq[3]));
+            const bf16x8 d1 = __builtin_bit_cast(bf16x8, make_uint4(dq[4], dq[5], dq[6], dq[7]));
+            dw1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ax0, d0, dw1, 0, 0, 0);
+            dw1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ax1, d1, dw1, 0, 0, 0);
         }
-        __syncthreads();                                // before the next step's tiles overwrite LDS
     }
     // ---- the workgroup's row of the workspace (plain stores) ----
     float *row = part + (size_t)blockIdx.x * (HP_MLP_PARAMS + 1);
-    for (int c = 0; c < 2; ++c) {
-        const int col = (2 * wave + c) * 32 + col_in;
-        for (int i = 0; i < 16; ++i) row[kOffW1 + d_row(i, half) * kH + col] = dw1[c][i];
-        // both halves of the wave hold partials of column col
-        const float w2s = dw2[c] + __shfl_xor(dw2[c], 32, 64);
-        const float b1s = db1[c] + __shfl_xor(db1[c], 32, 64);
-        if (half == 0) {
-            row[kOffW2 + col] = w2s;
-            row[kOffB1 + col] = b1s;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) row[kOffW1 + d_row(i, half) * kH + col] = dw1[i];
+    // both halves of the wave hold partials of column col
+    const float w2s = dw2 + __shfl_xor(dw2, 32, kWave);
+    const float b1s = db1 + __shfl_xor(db1, 32, kWave);
+    if (half == 0) {
+        row[kOffW2 + col] = w2s;
+        row[kOffB1 + col] = b1s;
+    }
+    // b2 and the loss: a fixed butterfly over the two waves that took rows
+    if (wave < 2) {
+        for (int off = 1; off < kWave; off <<= 1) {
+            db2 += __shfl_xor(db2, off, kWave);
+            lsum += __shfl_xor(lsum, off, kWave);
         }
-    }
-    // b2 and the loss: a fixed butterfly over the wave, then the waves in order
-    for (int off = 1; off < 64; off <<= 1) {
-        db2 += __shfl_xor(db2, off, 64);
-        lsum += __shfl_xor(lsum, off, 64);
-    }
-    if (lane == 0) {
-        s_red[wave][0] = db2;
-        s_red[wave][1] = lsum;
+        if (lane == 0) {
+            s_red[wave][0] = db2;
+            s_red[wave][1] = lsum;
+        }
     }
     __syncthreads();
     if (tid == 0) {
-        float b = s_red[0][0], l = s_red[0][1];
-        for (int w = 1; w < kWaves; ++w) {
-            b += s_red[w][0];
-            l += s_red[w][1];
-        }
-        row[kOffB2] = b;
-        row[HP_MLP_PARAMS] = l;
+        row[kOffB2] = s_red[0][0] + s_red[1][0];
+        row[HP_MLP_PARAMS] = s_red[0][1] + s_red[1][1];
     }
 }
 
@@ -377,6 +395,7 @@ __global__ __launch_bounds__(1024) void mlp_reduce_kernel(const float *__restric
     const int per = (parts + 15) / 16, lo = grp * per, hi = min(parts, lo + per);
     float sum = 0.0f;
     if (p <= HP_MLP_PARAMS)
+#pragma unroll 8
         for (int b = lo; b < hi; ++b) sum += part[(size_t)b * (HP_MLP_PARAMS + 1) + p];
     s[grp][c] = sum;
     __syncthreads();
@@ -515,14 +534,14 @@ hipError_t launch_features(const Plan &p, uint16_t *x, hipStream_t s) {
 
 hipError_t launch_mlp(const hp_mlp &net, const uint16_t *x, const float *y, int64_t rows, float *q, float *loss_sum,
                       bool backward, hipStream_t s) {
+    const int64_t steps = (rows + kStepRows - 1) / kStepRows;
     if (backward) {
-        // 128 rows per workgroup step; one workspace row per workgroup
-        const int grid = grid_for((rows + 127) / 128, 1, HP_MLP_PARTS);
-        mlp_backward_kernel<<<grid, kWaves * 64, 0, s>>>(x, y, rows, net.params, net.w_bf16, net.partials);
+        // one workspace row per workgroup
+        const int grid = grid_for(steps, 1, kMaxParts);
+        mlp_backward_kernel<<<grid, kBwdWaves * kWave, 0, s>>>(x, y, rows, net.params, net.w_bf16, net.partials);
         mlp_reduce_kernel<<<(HP_MLP_PARAMS + 1 + 63) / 64, 1024, 0, s>>>(net.partials, grid, net.grad, loss_sum);
     } else {
-        const int grid = grid_for((rows + 31) / 32, kWaves, 1024);
-        mlp_forward_kernel<<<grid, kWaves * 64, 0, s>>>(x, rows, net.params, net.w_bf16, q);
+        mlp_forward_kernel<<<grid_for(steps, 1, 1024), kFwdWaves * kWave, 0, s>>>(x, rows, net.params, net.w_bf16, q);
     }
     return hipGetLastError();
 }

@@ -94,3 +94,33 @@ def test_merge_at_tile_edges(hip, sizes, B, precision, alias):
         assert np.array_equal(v, want_v) and np.array_equal(nu, want_nu)
         assert np.array_equal(s_max, before[f][2]) and np.array_equal(best, before[f][3])
     plan.free()
+
+
+# rows at the edges of a tile of 32, a step of 128 and the 512 workgroups; the
+# bounds are those of the initializer's parity tests (FP32 sums of 256 products)
+@pytest.mark.parametrize("rows", [1, 31, 32, 127, 128, 129, 512 * 128, 512 * 128 + 1])
+def test_perceptron_rows_at_step_edges(hip, rows):
+    import torch
+    from paper_2311_02101_amd import learned as Lr
+    net = Lr.MLP(seed=17)
+    rng = np.random.default_rng(rows)
+    xf = M.bf16_round(rng.standard_normal((rows, M.F_IN)))
+    y = rng.uniform(0, 1, rows).astype(np.float32)
+    bits = torch.tensor((xf.astype(np.float32).view(np.uint32) >> 16).astype(np.uint16).view(np.int16), device="cuda")
+    p = net.host_params()
+    n1 = M.F_IN * M.HIDDEN
+    params = (p[:n1].reshape(M.F_IN, M.HIDDEN), p[n1:n1 + M.HIDDEN], p[n1 + M.HIDDEN:n1 + 2 * M.HIDDEN], p[-1])
+    say(f"[mlp] rows={rows}")
+    q = net.forward(bits)
+    loss = net.backward(bits, torch.tensor(y, device="cuda"))
+    torch.cuda.synchronize()
+    want, _ = M.forward(xf, *params)
+    assert np.max(np.abs(q.cpu().numpy() - want)) < 2e-6
+    g = M.gradients(xf, y.astype(np.float64), *params)
+    got = net.grad.cpu().numpy().astype(np.float64)
+    parts = dict(W1=got[:n1].reshape(M.F_IN, M.HIDDEN), b1=got[n1:n1 + M.HIDDEN],
+                 w2=got[n1 + M.HIDDEN:n1 + 2 * M.HIDDEN], b2=got[-1:])
+    for k, v in parts.items():
+        assert np.max(np.abs(v - g[k])) < 1e-4 * max(np.max(np.abs(g[k])), 1e-30), k
+    want_loss = M.loss(xf, y.astype(np.float64), *params) * rows
+    assert abs(float(loss.item()) - want_loss) < 1e-5 * abs(want_loss)
