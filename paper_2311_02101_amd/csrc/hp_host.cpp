@@ -149,7 +149,7 @@ void default_shape(const Plan &p, Bucket &bk, int threads, int max_lds, bool clu
         while (crowded < top && crowded * 1.4142 < (fp64 ? 5.0 : 6.5) * std::sqrt((double)bk.max_c)) crowded *= 2;
         int fill = kMaxThreads;
         // (a few workgroups per CU of a large formula only pay over several rounds)
-        if (r > 3 || (r == 3 && m > 2) || (r == 2 && m > 3 && !fp64))
+        if (r > 3 || (r == 3 && (m > 2 || bk.max_c < 12000)) || (r == 2 && m > 3 && !fp64))
             while (fill > kWave && std::min(m, r) * fill > res) fill /= 2;
         threads = std::max(crowded, fill);
         while (threads > kWave && threads / 4 >= bk.max_c) threads /= 2;
@@ -157,7 +157,7 @@ void default_shape(const Plan &p, Bucket &bk, int threads, int max_lds, bool clu
     bk.threads = threads;
     bk.vpt = vpt_for(bk, threads, p.cus, false, fp64);
     const bool alone = bk.count <= p.cus || 2 * bk.lds > (size_t)max_lds || threads == kMaxThreads;
-    bk.dyn = bk.max_c >= (alone ? 4 : 60) * threads ? 1 : 0;
+    bk.dyn = clust || bk.max_c >= (alone ? 4 : 60) * threads ? 1 : 0;
 }
 
 // Split a column of 8 weights into kLimbs BF16 limbs on the column's common
