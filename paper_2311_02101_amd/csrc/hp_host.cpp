@@ -713,8 +713,24 @@ hp_status hp_plan(hp_plan_t *out, const hp_cnf *cnf, const hp_rbm *rbm, const hp
             bk.kind = kBucketWide;        // the split kernel's table layout
             bk.lds = lds_bytes_push(bk.max_n, bk.kind, &bk.v_off, &bk.x_off);
         }
-        // resident workgroups of the variant a split of G members launches
-        auto capacity = [&](int G) { return (int64_t)p->cus * split_occupancy(*p, G); };
+        // resident workgroups of the variant a split of G members launches (for
+        // formulas whose tables fit in LDS no more than with them there, so
+        // plans keep their member counts and hp_run_noalloc its limit)
+        int32_t vo, xo;
+        const size_t lds_tables = lds_bytes_push(bk.max_n, kBucketPush, &vo, &xo);
+        const int fit = clust || need[0] != kBucketPush ? INT32_MAX : (int)((size_t)max_lds / lds_tables);
+        auto capacity = [&](int G) { return (int64_t)p->cus * std::min(split_occupancy(*p, G), fit); };
+        // larger formulas ran unsplit under hp_run_noalloc, whatever their
+        // chains: they split only as far as its scratch holds the mailboxes
+        p->nstride = ((int64_t)bk.max_n + 127) / 128 * 128;
+        auto scratch_fits = [&](int G) {
+            if (need[0] == kBucketPush) return true;
+            const int saved_split = p->split;
+            p->split = G;
+            const bool ok = run_scratch_bytes(*p) <= kScratchBytes;
+            p->split = saved_split;
+            return ok;
+        };
         const int n_items = bk.count;
         // every member owns at least one group of 4 variables
         int min_groups = INT32_MAX;
@@ -749,7 +765,7 @@ hp_status hp_plan(hp_plan_t *out, const hp_cnf *cnf, const hp_rbm *rbm, const hp
                        (g < 16 || (int64_t)n_items * g * 2 <= p->cus || bk.max_c / g >= 6144);
             };
             while (G * 2 <= kMaxSplit && G * 2 <= min_groups && (int64_t)n_items * G * 2 <= capacity(G * 2) &&
-                   pays(G * 2))
+                   pays(G * 2) && scratch_fits(G * 2))
                 G *= 2;
             if (G == 2 && work_c < 4096) G = 1;
         }

@@ -68,3 +68,26 @@ def test_pull_slices(hip, n, k, threads, hub, precision):
                 ost = R.run(ost, op, temps, S, alpha=1e-3, seed=52)
         compare_state(st.formula(0), (ost.v, ost.nu, ost.s_max, ost.best), "f64", f"n={n}", 1e-13)
     plan.free()
+
+
+# formulas whose tables do not fit in LDS beside them (above 13 600 variables) split
+# as far as hp_run_noalloc's scratch goes, and no call of theirs is refused
+@pytest.mark.parametrize("n,chains,precision", [(14000, 2, "f64"), (16384, 9, "f32"), (16500, 64, "f64")])
+def test_large_formulas_split_like_one_workgroup(hip, n, chains, precision):
+    T = wl.random_formula(n, 53)
+    W, b, _ = wl.pretrained_rbm(7, wl.FSTAR_PAIR)
+    temps = wl.default_temperatures(chains, 2)
+    v0 = [wl.initial_state(chains, n, 53)]
+    out = []
+    for split, noalloc in ((1, False), (0, False), (0, True)):
+        plan = hp.Plan([T], [n], W, b, chains=chains, temps=temps, precision=precision, seed=53, split=split)
+        say(f"[large split] n={n} chains={chains} {precision} split={plan.split} noalloc={noalloc}")
+        st = plan.new_state(v0)
+        (plan.run_noalloc if noalloc else plan.run)(st, 3)
+        plan.check()
+        out.append(st.formula(0) + (plan.split,))
+        plan.free()
+    assert out[0][4] == 1 and (out[1][4] > 1 or chains == 64)
+    for got in out[1:]:
+        for a, c in zip(out[0][:4], got[:4]):
+            assert np.array_equal(a, c)
