@@ -96,8 +96,9 @@ typedef struct {
     uint64_t seed;                  /* Philox key source                               */
     int32_t threads;                /* workgroup size override (0 = automatic)         */
     int32_t split;                  /* workgroups per chain of the push kernel: 0 =
-                                       automatic (fill the device), 1 = one, or a power
-                                       of two up to 16.  The plan admits a split only
+                                       automatic (up to filling the device, where the
+                                       exchange pays), 1 = one, or a power of two up
+                                       to 16.  The plan admits a split only
                                        if all its workgroups fit on the device at once
                                        and every formula has more than 4 (split - 1)
                                        variables (HP_EUNSUPPORTED otherwise); they
