@@ -128,46 +128,39 @@ __global__ __launch_bounds__(kFeatThreads) void feature_kernel(const uint4 *__re
 
 // ---- perceptron ---------------------------------------------------------------
 // Hidden layer on MFMA 32x32x16 bf16.  Lane l supplies index l%32 of an operand
-// (a row of A, a column of B) with k = (l/32)*8 + 0..7, the same registers for
-// either side; D[32 x 32]: register i -> row (i/4)*8 + (l/32)*4 + i%4, column
-// l%32.  The waves of a workgroup split the 256 hidden units in chunks of 32,
-// and a wave keeps its chunks' weights, biases and output weights in registers
-// for the whole launch.  With the weights as A and a tile of 32 data rows as B,
-// a lane holds 16 hidden units of one data row: the output dot product is a
-// maximum and a multiply-add per unit with no sum across lanes (the bias enters
-// as the product's C operand), then one add between the wave's halves and one
-// sum over the waves in LDS.
-constexpr int kStepRows = 128;   // data rows per workgroup step: 4 tiles
+// (a row of A, a column of B) with k = (l/32)*8 + 0..7; D[32 x 32]: register
+// i -> row (i/4)*8 + (l/32)*4 + i%4, column l%32.  A tile is 32 data rows (A)
+// against a chunk of 32 hidden units (B): a lane holds 16 rows of one unit.
+//
+// Order of a row's output sum, fixed (the initial draws compare 24-bit uniforms
+// with q, so another order of the same sum flips one draw in 80 million): unit
+// position p = l%32 sums relu(pre) w2 over the eight chunks in ascending order
+// (one fused multiply-add each, the bias added to the product before relu), then
+// the 32 positions are added as a balanced tree over the bits of p, lowest bit
+// first, and b2 last; all in FP32.
+constexpr int kStepRows = 128;   // data rows per step of the backward kernel: 4 tiles
+constexpr int kChunks = kH / 32;
+constexpr int kWStride = 40;     // halves per staged unit: 16-byte aligned, off the banks' period
 
 // row of D register i for lane half h (see above)
 __device__ __forceinline__ int d_row(int i, int h) { return (i / 4) * 8 + h * 4 + (i % 4); }
 
-// one hidden chunk's constants: weights (both k-steps; lane l%32 = unit), and
-// bias and output weight of the units in the lane's D registers
-struct HiddenChunk {
-    bf16x8 w0, w1;
-    f32x16 b1, w2;
+// The network in LDS: W1 transposed ([unit][feature], bfloat16), (b1, w2) per unit.
+struct NetLds {
+    __align__(16) uint16_t w1t[kH * kWStride];
+    float2 bw[kH];
 };
 
-__device__ __forceinline__ HiddenChunk load_chunk(const float *params, const uint16_t *wbf, int j, int lane) {
-    const int half = lane >> 5;
-    const uint16_t *w = wbf + (j * 32 + (lane & 31)) * kF + half * 8;
-    HiddenChunk c;
-    // element-wise: the caller's buffers are aligned to their elements only
-    uint32_t a[4], b[4];
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-        a[m] = (uint32_t)w[2 * m] | ((uint32_t)w[2 * m + 1] << 16);
-        b[m] = (uint32_t)w[16 + 2 * m] | ((uint32_t)w[16 + 2 * m + 1] << 16);
-    }
-    c.w0 = __builtin_bit_cast(bf16x8, make_uint4(a[0], a[1], a[2], a[3]));
-    c.w1 = __builtin_bit_cast(bf16x8, make_uint4(b[0], b[1], b[2], b[3]));
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        c.b1[i] = params[kOffB1 + j * 32 + d_row(i, half)];
-        c.w2[i] = bf16_value(wbf[kH * kF + j * 32 + d_row(i, half)]);
-    }
-    return c;
+__device__ __forceinline__ void load_net(NetLds &s, const float *params, const uint16_t *wbf, int tid, int NT) {
+    for (int i = tid; i < kH * kF; i += NT) s.w1t[(i / kF) * kWStride + i % kF] = wbf[i];
+    for (int i = tid; i < kH; i += NT) s.bw[i] = make_float2(params[kOffB1 + i], bf16_value(wbf[kH * kF + i]));
+}
+
+// this lane's two B operands (k-steps) of chunk j
+__device__ __forceinline__ void chunk_weights(const NetLds &s, int j, int lane, bf16x8 &w0, bf16x8 &w1) {
+    const uint16_t *w = &s.w1t[(j * 32 + (lane & 31)) * kWStride + (lane >> 5) * 8];
+    w0 = *reinterpret_cast<const bf16x8 *>(w);
+    w1 = *reinterpret_cast<const bf16x8 *>(w + 16);
 }
 
 // The two operands (k-steps) of the 32-row tile starting at row0: lane l
@@ -186,135 +179,166 @@ __device__ __forceinline__ void load_x_tile(const uint16_t *x, int64_t rows, int
     }
 }
 
-// w2 . relu(W1^T x + b1) of the tile's rows over the units of one chunk that
-// this half of the wave holds, in FP32; the sums of chunks, halves and waves are
-// taken in FP64 (a few additions per row, where FP32 ones would leave q 4%
-// further from the exact value than sums across the lanes do)
-__device__ __forceinline__ float chunk_logit(const HiddenChunk &c, bf16x8 x0, bf16x8 x1) {
-    f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c.w0, x0, c.b1, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c.w1, x1, acc, 0, 0, 0);
-    float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int i = 0; i < 16; ++i) s[i & 3] = fmaf(fmaxf(acc[i], 0.0f), c.w2[i], s[i & 3]);
-    return (s[0] + s[1]) + (s[2] + s[3]);
+// the value of x in the lane that a VALU lane permute names
+template <int kCtrl>
+__device__ __forceinline__ float dpp(float x) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), kCtrl, 0xf, 0xf, false));
 }
 
-// Forward: 4 waves of 64 units each.  Bound by the two VALU instructions per
-// row and unit: 524 288 rows take 25 us, 4 M rows 175 us (393 TFLOP/s of
-// products), before 39 and 264 us with rows as A, whose dot product needed a
-// five-step sum across the lanes for every row.
+// One level of the tree: of the 2 N sums the lane keeps N (the upper half if
+// `hi`) and adds the partner's, whose other half it sends in turn.
+template <int N, int kCtrl>
+__device__ __forceinline__ void tree_level(float (&s)[16], bool hi) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const float keep = hi ? s[i + N] : s[i], send = hi ? s[i] : s[i + N];
+        s[i] = keep + dpp<kCtrl>(send);
+    }
+}
+
+// D register whose row a lane holds after the tree.  The third level pairs
+// lanes l and 7 - l of every 8 (a mirror; there is no permute by 4), so in the
+// upper four the first two levels keep the opposite halves.
+__device__ __forceinline__ int tree_reg(int lane) {
+    const int q = (lane & 4) ? ~lane : lane;
+    return (q & 1) * 8 + (q & 2) * 2 + (lane >> 1 & 2) + (lane >> 3 & 1);
+}
+
+// Output logit (without b2) of row d_row(tree_reg(lane), lane / 32) of the tile,
+// the same in lanes l and l ^ 16.  Each level of the tree halves what a lane
+// holds (47 VALU instructions a tile, where a sum of every register in every
+// lane takes 80 lane permutes and adds).
+__device__ __forceinline__ float tile_logit(const NetLds &net, int lane, bf16x8 a0, bf16x8 a1) {
+    float s[16] = {};
+#pragma unroll 2
+    for (int j = 0; j < kChunks; ++j) {
+        bf16x8 w0, w1;
+        chunk_weights(net, j, lane, w0, w1);
+        f32x16 acc = {};
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, w0, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, w1, acc, 0, 0, 0);
+        const float2 bw = net.bw[j * 32 + (lane & 31)];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[i] = fmaf(fmaxf(acc[i] + bw.x, 0.0f), bw.y, s[i]);
+    }
+    const int q = (lane & 4) ? ~lane : lane;
+    tree_level<8, 0xB1>(s, (q & 1) != 0);        // quad_perm 1,0,3,2
+    tree_level<4, 0x4E>(s, (q & 2) != 0);        // quad_perm 2,3,0,1
+    tree_level<2, 0x141>(s, (lane & 4) != 0);    // row_half_mirror
+    tree_level<1, 0x128>(s, (lane & 8) != 0);    // row_ror:8
+    return s[0] + __shfl_xor(s[0], 16, kWave);
+}
+
+// Forward: a wave per tile.  Bound by the three VALU instructions per row and
+// unit that the order asks for: 524 288 rows take 21.4 us, 4 M rows 150 us (460
+// TFLOP/s of products); with every register summed over the lanes in every lane
+// 37.2 and 245 us; with the weights as A and other sums (bias in the product,
+// FP64 over the chunks) 24.6 and 172 us.
 constexpr int kFwdWaves = 4;
 
 __global__ __launch_bounds__(kFwdWaves *kWave) void mlp_forward_kernel(const uint16_t *__restrict__ x, int64_t rows,
                                                                        const float *__restrict__ params,
                                                                        const uint16_t *__restrict__ wbf,
                                                                        float *__restrict__ q_out) {
-    __shared__ double s_part[2][kFwdWaves][kStepRows];
+    __shared__ NetLds s_net;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    const HiddenChunk c0 = load_chunk(params, wbf, 2 * wave, lane), c1 = load_chunk(params, wbf, 2 * wave + 1, lane);
+    load_net(s_net, params, wbf, tid, kFwdWaves * kWave);
+    __syncthreads();
     const float b2 = params[kOffB2];
-    const int64_t n_steps = (rows + kStepRows - 1) / kStepRows;
-    int buf = 0;
-    for (int64_t step = blockIdx.x; step < n_steps; step += gridDim.x, buf ^= 1) {   // uniform over the workgroup
-        uint4 x0[4], x1[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) load_x_tile(x, rows, step * kStepRows + 32 * t, lane, x0[t], x1[t]);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const bf16x8 a0 = __builtin_bit_cast(bf16x8, x0[t]), a1 = __builtin_bit_cast(bf16x8, x1[t]);
-            double s = (double)chunk_logit(c0, a0, a1) + (double)chunk_logit(c1, a0, a1);
-            s += __shfl_xor(s, 32, kWave);
-            if (lane < 32) s_part[buf][wave][32 * t + lane] = s;
-        }
-        __syncthreads();          // (the other buffer's readers passed it before writing here again)
-        const int64_t r = step * kStepRows + tid;
-        if (tid < kStepRows && r < rows) {
-            const float o = (float)(((s_part[buf][0][tid] + s_part[buf][1][tid]) +
-                                     (s_part[buf][2][tid] + s_part[buf][3][tid])) + (double)b2);
-            q_out[r] = 1.0f / (1.0f + expf(-o));
-        }
+    const int row = d_row(tree_reg(lane), lane >> 5);
+    const int64_t n_tiles = (rows + 31) / 32;
+    for (int64_t tile = (int64_t)blockIdx.x * kFwdWaves + wave; tile < n_tiles; tile += (int64_t)gridDim.x * kFwdWaves) {
+        uint4 x0, x1;
+        load_x_tile(x, rows, tile * 32, lane, x0, x1);
+        const float o = tile_logit(s_net, lane, __builtin_bit_cast(bf16x8, x0), __builtin_bit_cast(bf16x8, x1)) + b2;
+        const int64_t r = tile * 32 + row;
+        if ((lane & 16) == 0 && r < rows) q_out[r] = 1.0f / (1.0f + expf(-o));
     }
 }
 
-// Backward: 8 waves of 32 units each, 128 rows per step.
-//   pass 1: logits as in the forward kernel; 128 threads then take one row each
-//           for q, the output gradient g = (q - y) / rows and the loss; the
-//           rows, and the rows transposed, go to LDS on the way;
-//   pass 2: with the rows as A and the wave's weights as B, a lane holds 16 rows
-//           of its unit: dh = g w2 relu'(pre) (bfloat16 for the product) adds
-//           x^T dh to the wave's dW1 chunk, g h to dw2 and dh to db1.
+// Backward: 8 waves, 128 rows (4 tiles) per step.
+//   pass 1: waves 0..3 take a tile each: logits as in the forward kernel, then q,
+//           the output gradient g = (q - y) / rows and the loss of the row that a
+//           lane holds; waves 4..7 bring the tiles' rows to LDS, as they are and
+//           transposed;
+//   pass 2: every wave, for its own 32 hidden units: with the rows as A and the
+//           units' weights as B, a lane holds 16 rows of its unit: dh = g w2
+//           relu'(pre) (bfloat16 for the product) adds x^T dh to the wave's dW1
+//           chunk, g h to dw2 and dh to db1.
 // The x^T dh product reuses the D layout as its B operand by ordering the
 // reduction index (the rows) as D does:
 // step s, k = (l/32)*8 + m  <->  row ((s*8 + m)/4)*8 + (l/32)*4 + m%4.
-// Each dW1 column is summed by one wave only; a workgroup writes its sums to a
-// row of the workspace, and half as many rows as before (512) halve what the
-// reduction below moves.  262 144 rows: 38 us and 5.3 us for the reduction,
-// before 77.7 and 21.1 (every wave computed the logits of its own tile with the
-// weights read from LDS, and summed them across the lanes).
+// Each dW1 column is summed by one wave only; a workgroup writes its sums to its
+// row of the workspace.  One barrier per step: rows and g have two buffers.
+// 262 144 rows take 45.6 us with the reduction below (36.8 and 8.6 under the
+// profiler), 4 M rows 384 us; before 93.1 and 1019 us (4 waves, all of them on
+// logits with the lane sums, weights from LDS in pass 2 too).  512 workgroups,
+// half the rows to reduce, would save 3.5 us of 45.6 but sum twice as many rows in
+// a row in FP32.
 constexpr int kBwdWaves = 8;
-constexpr int kMaxParts = 512;
 constexpr int kXStride = 40;      // halves per staged row: 16-byte aligned, off the banks' period
 constexpr int kXtStride = 36;     // halves per staged feature: 8-byte aligned
 
 __global__ __launch_bounds__(kBwdWaves *kWave) __attribute__((amdgpu_waves_per_eu(4))) void mlp_backward_kernel(
     const uint16_t *__restrict__ x, const float *__restrict__ y, int64_t rows, const float *__restrict__ params,
     const uint16_t *__restrict__ wbf, float *__restrict__ part) {
+    __shared__ NetLds s_net;
     __shared__ __align__(16) uint16_t s_x[2][4][32 * kXStride];       // tile rows: [row][feature]
     __shared__ __align__(16) uint16_t s_xt[2][4][kF * kXtStride];     // transposed: [feature][row]
-    __shared__ double s_part[kBwdWaves][kStepRows];
-    __shared__ __align__(16) float s_g[kStepRows];
-    __shared__ float s_red[2][2];
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    __shared__ __align__(16) float s_g[2][kStepRows];
+    __shared__ float s_red[4][2];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int half = lane >> 5, col_in = lane & 31, col = wave * 32 + col_in;
-    const HiddenChunk c = load_chunk(params, wbf, wave, lane);
-    const float b2 = params[kOffB2], bb = params[kOffB1 + col], ww = bf16_value(wbf[kH * kF + col]);
+    load_net(s_net, params, wbf, tid, kBwdWaves * kWave);
+    __syncthreads();
+    bf16x8 w0, w1;
+    chunk_weights(s_net, wave, lane, w0, w1);
+    const float b2 = params[kOffB2], bb = s_net.bw[col].x, ww = s_net.bw[col].y;
     const float inv_rows = 1.0f / (float)rows;
+    const int row_in = d_row(tree_reg(lane), half);
     const int64_t n_steps = (rows + kStepRows - 1) / kStepRows;
     f32x16 dw1 = {};
-    float dw2 = 0.0f, db1 = 0.0f, db2 = 0.0f, lsum = 0.0f;      // db2, lsum: threads 0..127, their rows' sums
+    float dw2 = 0.0f, db1 = 0.0f, db2 = 0.0f, lsum = 0.0f;      // db2, lsum: the lane's row in each of its tiles
     int buf = 0;
     for (int64_t step = blockIdx.x; step < n_steps; step += gridDim.x, buf ^= 1) {   // uniform over the workgroup
         // ---- pass 1 ----
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            uint4 x0, x1;
-            load_x_tile(x, rows, step * kStepRows + 32 * t, lane, x0, x1);
-            // waves 2t and 2t + 1 stage tile t: its features' first and second 16
-            if ((wave >> 1) == t) {
-                const uint4 v = (wave & 1) ? x1 : x0;
-                const int f0 = (wave & 1) * 16 + half * 8;
-                *reinterpret_cast<uint4 *>(&s_x[buf][t][col_in * kXStride + f0]) = v;
-                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                for (int m = 0; m < 8; ++m)
-                    s_xt[buf][t][(f0 + m) * kXtStride + col_in] = (uint16_t)(w[m >> 1] >> (16 * (m & 1)));
+        const int tile = wave & 3;
+        const int64_t row0 = step * kStepRows + 32 * tile;
+        uint4 x0, x1;
+        load_x_tile(x, rows, row0, lane, x0, x1);
+        if (wave < 4) {
+            const float o =
+                tile_logit(s_net, lane, __builtin_bit_cast(bf16x8, x0), __builtin_bit_cast(bf16x8, x1)) + b2;
+            if ((lane & 16) == 0) {
+                const int64_t r = row0 + row_in;
+                float g = 0.0f;
+                if (r < rows) {
+                    const float yy = y[r];
+                    const float qq = 1.0f / (1.0f + expf(-o));
+                    g = (qq - yy) * inv_rows;
+                    // softplus(o) - y o
+                    const float sp = o > 0.0f ? o + log1pf(expf(-o)) : log1pf(expf(o));
+                    lsum += sp - yy * o;
+                    db2 += g;
+                }
+                s_g[buf][32 * tile + row_in] = g;
             }
-            double s = (double)chunk_logit(c, __builtin_bit_cast(bf16x8, x0), __builtin_bit_cast(bf16x8, x1));
-            s += __shfl_xor(s, 32, kWave);
-            if (lane < 32) s_part[wave][32 * t + lane] = s;
-        }
-        __syncthreads();
-        if (tid < kStepRows) {
-            const int64_t r = step * kStepRows + tid;
-            float g = 0.0f;
-            if (r < rows) {
-                double p[kBwdWaves / 2];
+        } else {
+            uint16_t *xr = &s_x[buf][tile][col_in * kXStride + half * 8];
+            *reinterpret_cast<uint4 *>(xr) = x0;
+            *reinterpret_cast<uint4 *>(xr + 16) = x1;
+            const uint32_t v0[4] = {x0.x, x0.y, x0.z, x0.w}, v1[4] = {x1.x, x1.y, x1.z, x1.w};
 #pragma unroll
-                for (int w = 0; w < kBwdWaves / 2; ++w) p[w] = s_part[2 * w][tid] + s_part[2 * w + 1][tid];
-                const float o = (float)(((p[0] + p[1]) + (p[2] + p[3])) + (double)b2);
-                const float yy = y[r];
-                const float qq = 1.0f / (1.0f + expf(-o));
-                g = (qq - yy) * inv_rows;
-                // softplus(o) - y o
-                const float sp = o > 0.0f ? o + log1pf(expf(-o)) : log1pf(expf(o));
-                lsum += sp - yy * o;
-                db2 += g;
+            for (int m = 0; m < 8; ++m) {
+                s_xt[buf][tile][(half * 8 + m) * kXtStride + col_in] = (uint16_t)(v0[m >> 1] >> (16 * (m & 1)));
+                s_xt[buf][tile][(16 + half * 8 + m) * kXtStride + col_in] = (uint16_t)(v1[m >> 1] >> (16 * (m & 1)));
             }
-            s_g[tid] = g;
         }
+        // (the next step's pass 1 writes the other buffers, whose readers have
+        // passed this barrier)
         __syncthreads();
-        // ---- pass 2: the wave's units over the 4 tiles (the next step's
-        // pass 1 stages into the other buffers) ----
+        // ---- pass 2: the wave's units over the 4 tiles ----
 #pragma unroll 1
         for (int t = 0; t < 4; ++t) {
             const uint16_t *xr = &s_x[buf][t][col_in * kXStride + half * 8];
@@ -328,12 +352,12 @@ __global__ __launch_bounds__(kBwdWaves *kWave) __attribute__((amdgpu_waves_per_e
             const bf16x8 ax0 = __builtin_bit_cast(bf16x8, make_uint4(p[0].x, p[0].y, p[1].x, p[1].y));
             const bf16x8 ax1 = __builtin_bit_cast(bf16x8, make_uint4(p[2].x, p[2].y, p[3].x, p[3].y));
             f32x16 acc = {};
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, c.w0, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, c.w1, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, w0, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, w1, acc, 0, 0, 0);
             uint32_t dq[8];
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4) {
-                const float4 g4 = *reinterpret_cast<const float4 *>(&s_g[32 * t + q4 * 8 + half * 4]);
+                const float4 g4 = *reinterpret_cast<const float4 *>(&s_g[buf][32 * t + q4 * 8 + half * 4]);
                 const float g[4] = {g4.x, g4.y, g4.z, g4.w};
                 float dh[4];
 #pragma unroll
@@ -365,9 +389,10 @@ __global__ __launch_bounds__(kBwdWaves *kWave) __attribute__((amdgpu_waves_per_e
         row[kOffW2 + col] = w2s;
         row[kOffB1 + col] = b1s;
     }
-    // b2 and the loss: a fixed butterfly over the two waves that took rows
-    if (wave < 2) {
-        for (int off = 1; off < kWave; off <<= 1) {
+    // b2 and the loss: a balanced tree over a tile's rows, lowest bit of the row
+    // first (the lanes that differ in it: see tree_reg), then the tiles in order
+    if (wave < 4) {
+        for (int off : {8, 7, 32, 2, 1}) {
             db2 += __shfl_xor(db2, off, kWave);
             lsum += __shfl_xor(lsum, off, kWave);
         }
@@ -378,8 +403,8 @@ __global__ __launch_bounds__(kBwdWaves *kWave) __attribute__((amdgpu_waves_per_e
     }
     __syncthreads();
     if (tid == 0) {
-        row[kOffB2] = s_red[0][0] + s_red[1][0];
-        row[HP_MLP_PARAMS] = s_red[0][1] + s_red[1][1];
+        row[kOffB2] = ((s_red[0][0] + s_red[1][0]) + s_red[2][0]) + s_red[3][0];
+        row[HP_MLP_PARAMS] = ((s_red[0][1] + s_red[1][1]) + s_red[2][1]) + s_red[3][1];
     }
 }
 
@@ -534,14 +559,14 @@ hipError_t launch_features(const Plan &p, uint16_t *x, hipStream_t s) {
 
 hipError_t launch_mlp(const hp_mlp &net, const uint16_t *x, const float *y, int64_t rows, float *q, float *loss_sum,
                       bool backward, hipStream_t s) {
-    const int64_t steps = (rows + kStepRows - 1) / kStepRows;
     if (backward) {
         // one workspace row per workgroup
-        const int grid = grid_for(steps, 1, kMaxParts);
+        const int grid = grid_for((rows + kStepRows - 1) / kStepRows, 1, HP_MLP_PARTS);
         mlp_backward_kernel<<<grid, kBwdWaves * kWave, 0, s>>>(x, y, rows, net.params, net.w_bf16, net.partials);
         mlp_reduce_kernel<<<(HP_MLP_PARAMS + 1 + 63) / 64, 1024, 0, s>>>(net.partials, grid, net.grad, loss_sum);
     } else {
-        mlp_forward_kernel<<<grid_for(steps, 1, 1024), kFwdWaves * kWave, 0, s>>>(x, rows, net.params, net.w_bf16, q);
+        mlp_forward_kernel<<<grid_for((rows + 31) / 32, kFwdWaves, 1024), kFwdWaves * kWave, 0, s>>>(
+            x, rows, net.params, net.w_bf16, q);
     }
     return hipGetLastError();
 }
