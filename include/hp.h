@@ -105,7 +105,15 @@ typedef struct {
                                        exchange data every sweep, so a split run must
                                        not share the device with work that keeps CUs
                                        occupied for long (its bounded waits for the
-                                       other workgroups would time out: hp_check)    */
+                                       other workgroups would time out: hp_check).
+                                       Formulas of more than about 13 600 variables,
+                                       whose tables do not fit in LDS beside them, take
+                                       no explicit split.  The automatic one of a batch
+                                       of those may share the device: the workgroups
+                                       of a chain wait a few milliseconds for each
+                                       other before its first sweep, and a chain whose
+                                       workgroups do not get together runs in one
+                                       workgroup behind the others, same bits       */
     int32_t kernel;                 /* hp_kernel: sweep kernel variant                 */
     int32_t graph;                  /* 1: hp_run replays a captured hipGraph of its
                                        launches (cached per state buffers and sweep
@@ -124,7 +132,10 @@ typedef struct {
                                        another workgroup's data before giving up;
                                        > 0 = reloads of a word before giving up (a
                                        tiny limit forces the failure path that
-                                       hp_check reports, for tests)                  */
+                                       hp_check reports, for tests; above 13 600
+                                       variables, where the workgroups of a chain get
+                                       together first, it is that wait's limit and
+                                       forces the run in one workgroup)              */
 } hp_opts;
 
 typedef enum {

@@ -75,6 +75,8 @@ void release(Plan *p) {
     (void)hipFree(p->d_xpart);
     (void)hipFree(p->d_vbuf);
     (void)hipFree(p->d_cnt);
+    (void)hipFree(p->d_rec_solo);
+    (void)hipFree(p->d_orig_solo);
     (void)hipFree(p->d_err);
     (void)hipFree(p->d_temp);
     (void)hipFree(p->d_fe);
@@ -699,11 +701,17 @@ hp_status hp_plan(hp_plan_t *out, const hp_cnf *cnf, const hp_rbm *rbm, const hp
 
     // --- split: G co-resident workgroups per chain, single push bucket only ---
     int G = 1;
-    // (an explicit split asks for formulas whose tables would fit in LDS)
     const bool one_push = p->buckets.size() == 1 && p->buckets[0].kind != kBucketPull && !mixed;
-    if (opts->split >= 2 && !(one_push && need[0] == kBucketPush)) {
+    // Formulas whose tables do not fit in LDS beside them have run unsplit, on a
+    // device shared with any other work.  An explicit split of theirs is
+    // refused; the automatic one joins its members first and leaves the
+    // chains whose members do not get together to one workgroup each.
+    const bool large = need[0] != kBucketPush;
+    if (opts->split >= 2 && (!one_push || large)) {
         release(p);
-        return fail(HP_EUNSUPPORTED, "split needs a batch whose formulas all share one push launch");
+        return fail(HP_EUNSUPPORTED, one_push ? "an explicit split needs formulas whose tables fit in LDS beside them "
+                                                "(about 13 600 variables)"
+                                              : "split needs a batch whose formulas all share one push launch");
     }
     if (one_push && opts->split != 1 && !opts->graph) {
         Bucket &bk = p->buckets[0];
@@ -718,17 +726,18 @@ hp_status hp_plan(hp_plan_t *out, const hp_cnf *cnf, const hp_rbm *rbm, const hp
         // plans keep their member counts and hp_run_noalloc its limit)
         int32_t vo, xo;
         const size_t lds_tables = lds_bytes_push(bk.max_n, kBucketPush, &vo, &xo);
-        const int fit = clust || need[0] != kBucketPush ? INT32_MAX : (int)((size_t)max_lds / lds_tables);
+        const int fit = clust || large ? INT32_MAX : (int)((size_t)max_lds / lds_tables);
         auto capacity = [&](int G) { return (int64_t)p->cus * std::min(split_occupancy(*p, G), fit); };
         // larger formulas ran unsplit under hp_run_noalloc, whatever their
         // chains: they split only as far as its scratch holds the mailboxes
         p->nstride = ((int64_t)bk.max_n + 127) / 128 * 128;
         auto scratch_fits = [&](int G) {
-            if (need[0] == kBucketPush) return true;
-            const int saved_split = p->split;
+            if (!large) return true;
             p->split = G;
+            p->solo = 1;
             const bool ok = run_scratch_bytes(*p) <= kScratchBytes;
-            p->split = saved_split;
+            p->split = 1;
+            p->solo = 0;
             return ok;
         };
         const int n_items = bk.count;
@@ -755,8 +764,9 @@ hp_status hp_plan(hp_plan_t *out, const hp_cnf *cnf, const hp_rbm *rbm, const hp
             // work (a clause of one Philox block counts 0.6): 3000 clauses for
             // four members, 4096 for two, whose exchange costs as much (us per
             // sweep, 1 workgroup / split: 600 variables x 100 chains 5.1 / 5.3;
-            // 1027 x 32 7.9 / 5.3; 3 literals, 1027 x 128 5.0 / 5.4; 16384 x 64
-            // 84.8 / 40.6).  Sixteen members exchange more than they save unless
+            // 1027 x 32 7.9 / 5.3; 3 literals, 1027 x 128 5.0 / 5.4; joined splits
+            // of 16384 x 32, two members 89.9 / 58.0, of 14000 x 16, eight 82.7 /
+            // 17.6, one sweep alone 95.7 / 49.6).  Sixteen members exchange more than they save unless
             // they are few or have much to do each (8 / 16 members: 4096 x 16
             // 7.9 / 8.5, 8192 x 16 11.3 / 12.1, 8192 x 3 11.2 / 10.2).
             const double work_c = bk.max_c * (clust || L > 4 ? 1.0 : 0.6);
@@ -765,15 +775,23 @@ hp_status hp_plan(hp_plan_t *out, const hp_cnf *cnf, const hp_rbm *rbm, const hp
                        (g < 16 || (int64_t)n_items * g * 2 <= p->cus || bk.max_c / g >= 6144);
             };
             while (G * 2 <= kMaxSplit && G * 2 <= min_groups && (int64_t)n_items * G * 2 <= capacity(G * 2) &&
-                   pays(G * 2) && scratch_fits(G * 2))
+                   pays(G * 2) && scratch_fits(G * 2) && !(large && saved.grid))
                 G *= 2;
             if (G == 2 && work_c < 4096) G = 1;
         }
         if (G == 1) bk = saved;           // no split: keep the bucket's own shape
         else bk.grid = 0;                 // split launches run one item per group
+        p->solo = G > 1 && large ? 1 : 0;
+        p->solo_bucket = saved;
     }
     p->split = G;
     p->wait_limit = opts->split_wait_limit;
+    std::vector<uint4> rec_solo;
+    std::vector<uint32_t> orig_solo;
+    if (p->solo) {
+        rec_solo = rec;
+        orig_solo = orig;
+    }
     if (G > 1) {
         // member-major record order: member g of a split chain takes every
         // G-th record of the length-sorted order (the same length mix for
@@ -826,6 +844,12 @@ hp_status hp_plan(hp_plan_t *out, const hp_cnf *cnf, const hp_rbm *rbm, const hp
     orig.resize((size_t)NC + kWave);
     HP_TRY(upload(&p->d_rec, rec, s), "upload clause records");
     HP_TRY(upload(&p->d_orig, orig, s), "upload clause order");
+    if (p->solo) {
+        rec_solo.resize((size_t)NC + kWave);
+        orig_solo.resize((size_t)NC + kWave);
+        HP_TRY(upload(&p->d_rec_solo, rec_solo, s), "upload clause records (unsplit order)");
+        HP_TRY(upload(&p->d_orig_solo, orig_solo, s), "upload clause order (unsplit order)");
+    }
     HP_TRY(upload(&p->d_negcnt, negcnt, s), "upload negation counts");
     HP_TRY(upload(&p->d_temp, temp, s), "upload temperatures");
     std::vector<VarTile> tiles;
@@ -892,7 +916,7 @@ hp_status hp_plan(hp_plan_t *out, const hp_cnf *cnf, const hp_rbm *rbm, const hp
         const size_t items = (size_t)p->buckets[0].count;
         HP_TRY(hipMalloc((void **)&p->d_xpart, items * p->split * p->nstride * sizeof(int64_t)), "alloc xpart");
         HP_TRY(hipMalloc((void **)&p->d_vbuf, items * p->nstride), "alloc vbuf");
-        HP_TRY(hipMalloc((void **)&p->d_cnt, items * 2 * kMaxSplit * sizeof(int32_t)), "alloc counts");
+        HP_TRY(hipMalloc((void **)&p->d_cnt, count_bytes(*p)), "alloc counts");
     }
     HP_TRY(launch_tables(*p, s), "table kernel");
     // set-up of hp_run_noalloc: this device's address of the static scratch

@@ -183,7 +183,13 @@ struct SplitParams {
     uint32_t wait_limit;         // reloads of a mailbox word before giving up
     int32_t xcd_map;             // members of an item on the same XCD
     int32_t n_xcd;
+    uint32_t *join;              // [items] members arrived, or nullptr: no join (Plan::solo)
+    uint32_t join_limit;         // reloads of a join word before the item is closed
 };
+
+// A closed join word: the item's members did not all arrive in time and left
+// its state alone; the launch behind the split one runs it.
+constexpr uint32_t kJoinClosed = 0x80000000u;
 
 enum class Variant { kPull = 0, kPush = 1 };
 
@@ -205,6 +211,7 @@ struct WorkQueue {
     uint32_t *ctr;               // [kXcds][32] counters, zeroed before the launch
     int32_t count;               // items of the launch
     int32_t xq[kXcds + 1];       // item ranges per XCD
+    const uint32_t *join;        // without counters: run only the items whose join word is closed (nullptr: all)
 };
 
 enum BucketKind : int32_t { kBucketPush = 0, kBucketWide = 1, kBucketPull = 2, kBucketMid = 3 };
@@ -248,6 +255,10 @@ struct Plan {
     int32_t cus = 0;             // compute units of the device
     std::vector<Bucket> buckets;
     int32_t split = 1;           // G workgroups per chain (single push bucket only)
+    // 1: a split whose members join before their first sweep; the items that
+    // do not get together run in `solo_bucket`, one workgroup each
+    int32_t solo = 0;
+    Bucket solo_bucket;
     int32_t wait_limit = 0;      // split: mailbox reloads before giving up (0 = default)
     int32_t xcd_map = 0;
     int64_t nstride = 0;
@@ -281,6 +292,8 @@ struct Plan {
     uint32_t *d_ell_deg = nullptr;        //   list lengths
     uint4 *d_rec = nullptr;
     uint32_t *d_orig = nullptr;
+    uint4 *d_rec_solo = nullptr;          // solo: the records in the unsplit order
+    uint32_t *d_orig_solo = nullptr;
     int32_t *d_negcnt = nullptr;
     int32_t *d_tabflag = nullptr;
     int32_t *d_temp = nullptr;            // [F][B]
@@ -305,13 +318,15 @@ struct RunBuffers {
     uint32_t *queue;             // [kMaxBuckets][kQueueWords] work counters
     int64_t *xpart;              // split: [items][G][nstride] partial logits
     uint8_t *vbuf;               // split: [items][nstride] packed new values
-    int32_t *cnt;                // split: [items][2][kMaxSplit] partial counts
+    int32_t *cnt;                // split: [items][2][kMaxSplit] partial counts, solo: then [items] join words
     // the sweep counter at the run's start (in the first counter line, beside
     // the counter itself)
     int64_t *t0() const { return reinterpret_cast<int64_t *>(queue + 16); }
 };
 constexpr size_t kScratchBytes = size_t(16) << 20;
 RunBuffers plan_buffers(const Plan &p);
+// split: bytes of the partial counts and join words (a multiple of 16)
+size_t count_bytes(const Plan &p);
 // bytes of static scratch a run of this plan needs, and its layout there
 size_t run_scratch_bytes(const Plan &p);
 RunBuffers scratch_buffers(const Plan &p, void *base);

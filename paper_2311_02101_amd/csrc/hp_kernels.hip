@@ -1146,7 +1146,8 @@ __device__ __forceinline__ void push_sweeps(const SweepParams<Real> &P, const Pu
 // range first, so the workgroups that share an L2 run the chains of the same
 // few formulas and their clause records stay in that L2, then it helps the
 // other ranges in turn.
-template <typename Real, int VPT, int kTab, bool kMfma = false, bool kClust = false>
+// kSolo: runs the items whose join word is closed (behind a split launch).
+template <typename Real, int VPT, int kTab, bool kMfma = false, bool kClust = false, bool kSolo = false>
 __global__ __launch_bounds__(1024) void sweep_push_kernel(SweepParams<Real> P, WorkQueue Q) {
     extern __shared__ __align__(16) unsigned char lds[];
     int *s_item = reinterpret_cast<int *>(lds + (kClust                  ? kClustCntOff
@@ -1154,6 +1155,7 @@ __global__ __launch_bounds__(1024) void sweep_push_kernel(SweepParams<Real> P, W
                                                  : kTab == kBucketMid  ? kMidCntOff
                                                                        : kPushCntOff)) +
                   63;
+    if (kSolo && (Q.join[blockIdx.x] & kJoinClosed) == 0u) return;
     const int tid = threadIdx.x, NT = blockDim.x;
     const bool sample = P.n_sweeps > 0;
     const int64_t S = sample ? P.n_sweeps : 1;
@@ -1514,6 +1516,28 @@ __device__ __forceinline__ T await_tag(const T *p, T e, uint32_t want, TagOf tag
     return e;
 }
 
+// Members of an item get together before its first sweep (thread 0; bounded).
+// A member adds itself to the item's join word and waits for it to reach G; the
+// one that has waited for too long closes the word.  An addition and a closing
+// are ordered on the word, so either all G members see G, and from then on all
+// of them are resident and every wait of the exchange ends, or all of them see
+// the word closed and leave with the item's state untouched.
+constexpr uint32_t kJoinSpins = 1u << 12;   // default limit: a few milliseconds
+
+__device__ __forceinline__ bool join_members(uint32_t *word, uint32_t G, uint32_t limit) {
+    uint32_t w = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
+    for (uint32_t spins = 0; w < G; ++spins) {                  // (a closed word is above G)
+        if (spins < limit) {
+            __builtin_amdgcn_s_sleep(1);
+            w = xload(word);
+        } else if (__hip_atomic_compare_exchange_strong(word, &w, w | kJoinClosed, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                        __HIP_MEMORY_SCOPE_AGENT)) {
+            return false;
+        }
+    }
+    return w == G;
+}
+
 // The sweeps of one member.  Member g owns variable groups [q_lo, q_hi) (of
 // 4): it keeps its own partial logits of those in LDS, publishes the others,
 // sums the G partials of its own variables exactly (integers), draws their new
@@ -1666,7 +1690,8 @@ __device__ __forceinline__ void split_sweeps(const SweepParams<Real> &P, const S
     }
 }
 
-template <typename Real, int VPT, bool kClust = false>
+// kJoin: the members of an item get together first (Plan::solo).
+template <typename Real, int VPT, bool kClust = false, bool kJoin = false>
 __global__ __launch_bounds__(1024) void sweep_split_kernel(SweepParams<Real> P, SplitParams Q) {
     extern __shared__ __align__(16) unsigned char lds[];
     SplitCtx<Real> c;
@@ -1686,10 +1711,18 @@ __global__ __launch_bounds__(1024) void sweep_split_kernel(SweepParams<Real> P, 
     }
     item = __builtin_amdgcn_readfirstlane(item);
     g = __builtin_amdgcn_readfirstlane(g);
+    const int tid = threadIdx.x, NT = blockDim.x;
+    if (kJoin) {
+        int *s_go = reinterpret_cast<int *>(lds);
+        if (tid == 0) *s_go = join_members(Q.join + item, (uint32_t)G, Q.join_limit) ? 1 : 0;
+        __syncthreads();
+        const int go = __builtin_amdgcn_readfirstlane(*s_go);
+        __syncthreads();                 // the tables go there
+        if (go == 0) return;
+    }
     const WorkItem w = P.work[item];
     const FormulaDev fd = P.fd[w.f];
     const int N = fd.n;
-    const int tid = threadIdx.x, NT = blockDim.x;
     const int tau = P.temp_of_chain[(int64_t)w.f * P.B + w.b];
     c.L = kClust ? push_lds_clust(lds, P.lds_x_off) : push_lds_for<kSplitTab<kClust>>(lds, P.lds_x_off, P.gfx, tau);
     const PushLds &L = c.L;
@@ -1870,7 +1903,11 @@ const void *clust_kernel_ptr(int vpt) {
 
 // owned variables per thread of a split member: 1 or 2 in registers, else 0
 template <typename Real>
-const void *split_kernel_ptr(bool clust, int vpt) {
+const void *split_kernel_ptr(bool clust, int vpt, bool join = false) {
+    if (join)
+        return vpt == 1 ? (const void *)sweep_split_kernel<Real, 1, false, true>
+               : vpt == 2 ? (const void *)sweep_split_kernel<Real, 2, false, true>
+                          : (const void *)sweep_split_kernel<Real, 0, false, true>;
     if (clust)
         return vpt == 1 ? (const void *)sweep_split_kernel<Real, 1, true>
                : vpt == 2 ? (const void *)sweep_split_kernel<Real, 2, true>
@@ -1878,6 +1915,18 @@ const void *split_kernel_ptr(bool clust, int vpt) {
     return vpt == 1 ? (const void *)sweep_split_kernel<Real, 1>
            : vpt == 2 ? (const void *)sweep_split_kernel<Real, 2>
                       : (const void *)sweep_split_kernel<Real, 0>;
+}
+
+// formulas above 13 600 variables hold the averages of 4 groups in FP32 on 1024
+// threads, else none
+template <typename Real>
+const void *solo_kernel_ptr(int vpt, int kind) {
+    constexpr int V = sizeof(Real) == 4 ? 4 : 0;
+    if (kind == kBucketMid)
+        return vpt == V ? (const void *)sweep_push_kernel<Real, V, kBucketMid, false, false, true>
+                        : (const void *)sweep_push_kernel<Real, 0, kBucketMid, false, false, true>;
+    return vpt == V ? (const void *)sweep_push_kernel<Real, V, kBucketWide, false, false, true>
+                    : (const void *)sweep_push_kernel<Real, 0, kBucketWide, false, false, true>;
 }
 
 const void *mixed_kernel_ptr(int vpt) {
@@ -1904,7 +1953,10 @@ hipError_t set_limits_t(int bytes) {
         ks.push_back(pull_kernel_ptr<Real>(vpt));
         ks.push_back(split_kernel_ptr<Real>(false, vpt));
         ks.push_back(split_kernel_ptr<Real>(true, vpt));
+        ks.push_back(split_kernel_ptr<Real>(false, vpt, true));
     }
+    for (int vpt : {0, 4})
+        for (int kind : {(int)kBucketWide, (int)kBucketMid}) ks.push_back(solo_kernel_ptr<Real>(vpt, kind));
     for (const void *k : ks) {
         hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
         if (e != hipSuccess) return e;
@@ -1957,7 +2009,7 @@ hipError_t launch_split_one(const Plan &p, SweepParams<Real> P, SplitParams Q, i
     // The plan checked that all count*G workgroups fit on the device at once
     // (occupancy x CUs), so on an otherwise idle device they are all resident
     // together; the waits for the other members are bounded either way (see hp_check).
-    hipLaunchKernelGGL((void (*)(SweepParams<Real>, SplitParams))split_kernel_ptr<Real>(p.clust, vpt),
+    hipLaunchKernelGGL((void (*)(SweepParams<Real>, SplitParams))split_kernel_ptr<Real>(p.clust, vpt, p.solo),
                        dim3(b.count * p.split), dim3(b.threads), b.lds, s, P, Q);
     return hipGetLastError();
 }
@@ -2032,6 +2084,16 @@ RunBuffers plan_buffers(const Plan &p) { return RunBuffers{p.d_queue, p.d_xpart,
 
 static size_t align256(size_t n) { return (n + 255) / 256 * 256; }
 
+size_t count_bytes(const Plan &p) {
+    const size_t items = (size_t)p.buckets[0].count;
+    return (items * 2 * kMaxSplit + (p.solo ? (items + 3) / 4 * 4 : 0)) * sizeof(int32_t);
+}
+
+// the join words behind the partial counts (Plan::solo)
+static uint32_t *join_words(const Plan &p, const RunBuffers &rb) {
+    return reinterpret_cast<uint32_t *>(rb.cnt) + (size_t)p.buckets[0].count * 2 * kMaxSplit;
+}
+
 // layout: work counters | xpart | vbuf | counts, each 256-byte aligned
 static void scratch_layout(const Plan &p, size_t off[4], size_t *total) {
     const size_t items = p.split > 1 ? (size_t)p.buckets[0].count : 0;
@@ -2039,7 +2101,7 @@ static void scratch_layout(const Plan &p, size_t off[4], size_t *total) {
     off[1] = align256(off[0] + (size_t)kMaxBuckets * kQueueWords * sizeof(uint32_t));
     off[2] = align256(off[1] + items * p.split * p.nstride * sizeof(int64_t));
     off[3] = align256(off[2] + items * p.nstride);
-    *total = align256(off[3] + items * 2 * kMaxSplit * sizeof(int32_t));
+    *total = align256(off[3] + (p.split > 1 ? count_bytes(p) : 0));
 }
 
 size_t run_scratch_bytes(const Plan &p) {
@@ -2059,9 +2121,13 @@ RunBuffers scratch_buffers(const Plan &p, void *base) {
 
 template <typename Real>
 hipError_t launch_bucket_t(const Plan &p, const Bucket &b, const hp_state &st, int64_t n_sweeps, hipStream_t s,
-                           uint32_t *queues, const int64_t *t_ptr) {
+                           uint32_t *queues, const int64_t *t_ptr, const uint32_t *join) {
     if (b.count == 0) return hipSuccess;
     SweepParams<Real> P = sweep_params<Real>(p, st, n_sweeps, t_ptr);
+    if (join) {                  // the items a split launch left
+        P.rec = p.d_rec_solo;
+        P.orig = p.d_orig_solo;
+    }
     P.work = p.d_work + b.first;
     P.lds_v_off = b.v_off;
     P.lds_x_off = b.x_off;
@@ -2074,6 +2140,7 @@ hipError_t launch_bucket_t(const Plan &p, const Bucket &b, const hp_state &st, i
     }
     WorkQueue Q;
     Q.ctr = nullptr;
+    Q.join = join;
     Q.count = b.count;
     for (int x = 0; x <= kXcds; ++x) Q.xq[x] = b.xq[x];
     int grid = b.count;
@@ -2082,7 +2149,8 @@ hipError_t launch_bucket_t(const Plan &p, const Bucket &b, const hp_state &st, i
         Q.ctr = queues + kQueueWords * (size_t)(&b - p.buckets.data());
         grid = b.grid;
     }
-    const void *kern = p.precision == HP_MIXED_BF16 ? mixed_kernel_ptr(b.vpt)
+    const void *kern = join                          ? solo_kernel_ptr<Real>(b.vpt, b.kind)
+                       : p.precision == HP_MIXED_BF16 ? mixed_kernel_ptr(b.vpt)
                        : p.clust                     ? clust_kernel_ptr<Real>(b.vpt)
                                                      : push_kernel_ptr<Real>(b.vpt, b.kind);
     hipLaunchKernelGGL((void (*)(SweepParams<Real>, WorkQueue))kern, dim3(grid), dim3(b.threads), b.lds, s, P, Q);
@@ -2090,9 +2158,9 @@ hipError_t launch_bucket_t(const Plan &p, const Bucket &b, const hp_state &st, i
 }
 
 static hipError_t launch_bucket_q(const Plan &p, const Bucket &b, const hp_state &st, int64_t n_sweeps, hipStream_t s,
-                                  const RunBuffers &rb, const int64_t *t_ptr) {
-    return p.precision == HP_FP32 ? launch_bucket_t<float>(p, b, st, n_sweeps, s, rb.queue, t_ptr)
-                                  : launch_bucket_t<double>(p, b, st, n_sweeps, s, rb.queue, t_ptr);
+                                  const RunBuffers &rb, const int64_t *t_ptr, const uint32_t *join = nullptr) {
+    return p.precision == HP_FP32 ? launch_bucket_t<float>(p, b, st, n_sweeps, s, rb.queue, t_ptr, join)
+                                  : launch_bucket_t<double>(p, b, st, n_sweeps, s, rb.queue, t_ptr, join);
 }
 
 hipError_t launch_bucket(const Plan &p, const Bucket &b, const hp_state &st, int64_t n_sweeps, hipStream_t s) {
@@ -2117,9 +2185,12 @@ hipError_t launch_split_t(const Plan &p, const hp_state &st, int64_t n_sweeps, h
     Q.err = p.d_err;
     Q.nstride = p.nstride;
     Q.G = p.split;
-    Q.wait_limit = p.wait_limit > 0 ? (uint32_t)p.wait_limit : kMailSpins;
+    // (with a join the caller's limit is the join's: members that got together do not give up)
+    Q.wait_limit = p.wait_limit > 0 && !p.solo ? (uint32_t)p.wait_limit : kMailSpins;
     Q.xcd_map = p.xcd_map;
     Q.n_xcd = 8;
+    Q.join = p.solo ? join_words(p, rb) : nullptr;
+    Q.join_limit = p.wait_limit > 0 ? (uint32_t)p.wait_limit : kJoinSpins;
     return launch_split_one<Real>(p, P, Q, split_vpt(b.max_n, p.split, b.threads), s);
 }
 
@@ -2139,6 +2210,7 @@ static hipError_t launch_buckets(const Plan &p, const hp_state &st, int64_t n_sw
     if (p.split > 1) {
         e = p.precision == HP_FP64 ? launch_split_t<double>(p, st, n_sweeps, s, rb)
                                    : launch_split_t<float>(p, st, n_sweeps, s, rb);
+        if (e == hipSuccess && p.solo) e = launch_bucket_q(p, p.solo_bucket, st, n_sweeps, s, rb, t_ptr, join_words(p, rb));
     } else if (p.buckets.size() == 1 || !p.forked) {
         for (size_t i = 0; i < p.buckets.size() && e == hipSuccess; ++i)
             e = launch_bucket_q(p, p.buckets[i], st, n_sweeps, s, rb, t_ptr);
@@ -2167,7 +2239,7 @@ hipError_t launch_sweep(const Plan &p, const hp_state &st, int64_t n_sweeps, hip
         const size_t items = (size_t)p.buckets[0].count;
         add(1, rb.xpart, items * p.split * p.nstride * sizeof(int64_t));
         add(2, rb.vbuf, items * p.nstride);
-        add(3, rb.cnt, items * 2 * kMaxSplit * sizeof(int32_t));
+        add(3, rb.cnt, count_bytes(p));
     } else {
         for (const Bucket &b : p.buckets)
             if (b.grid > 0) add(0, rb.queue, p.buckets.size() * kQueueWords * sizeof(uint32_t));
