@@ -1860,6 +1860,11 @@ __global__ __launch_bounds__(256) void begin_run_kernel(ZeroRanges Z, int64_t *t
             if (r != 0 || (i % (kQueueWords / 4)) % 8 == 0) Z.ptr[r][i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
+// takes begin_run_kernel's advance back (a launch behind it failed)
+__global__ void restore_t_kernel(int64_t *t, const int64_t *t0) {
+    if (threadIdx.x == 0 && blockIdx.x == 0) t[0] = t0[0];
+}
+
 __global__ void advance_t_kernel(int64_t *t, int64_t n) {
     if (threadIdx.x == 0 && blockIdx.x == 0) t[0] += n;
 }
@@ -2246,8 +2251,14 @@ hipError_t launch_sweep(const Plan &p, const hp_state &st, int64_t n_sweeps, hip
     }
     if (most > 0) {
         begin_run_kernel<<<(int)std::min<int64_t>((most + 255) / 256, 2048), 256, 0, s>>>(Z, st.t, rb.t0(), n_sweeps);
-        const hipError_t e = hipGetLastError();
-        return e == hipSuccess ? launch_buckets(p, st, n_sweeps, s, rb, rb.t0()) : e;
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        e = launch_buckets(p, st, n_sweeps, s, rb, rb.t0());
+        if (e != hipSuccess) {
+            restore_t_kernel<<<1, 64, 0, s>>>(st.t, rb.t0());
+            (void)hipGetLastError();
+        }
+        return e;
     }
     // nothing to clear: the kernels read the state's counter, which advances
     // after them
