@@ -557,10 +557,15 @@ hp_status hp_plan(hp_plan_t *out, const hp_cnf *cnf, const hp_rbm *rbm, const hp
         cls[f] = size_class(f);
     }
     // Occurrence lists of the pull formulas: per variable (c, k) ascending over
-    // all K slots (padding copies too: the pull sum adds them one by one),
-    // the lists of 64 consecutive variables interleaved.
+    // all K slots (padding copies too: the pull sum adds them one by one).
+    // The lists of 64 consecutive variables (a slice) are interleaved and padded
+    // to the longest of them, except for lists above four times the slice's
+    // mean and 16 entries, which stand by themselves.  So padding takes at most
+    // three times the words of the occurrences, or 16 entries a variable (with
+    // one variable in every clause it would take 63 times its list).  Four times
+    // the mean leaves the lists of a random formula together.
     std::vector<uint32_t> ell, ell_slice, ell_deg;
-    {
+    try {
         int64_t n_slices = 0;
         for (int f = 0; f < F; ++f)
             if (kind[f] == kBucketPull) {
@@ -568,48 +573,59 @@ hp_status hp_plan(hp_plan_t *out, const hp_cnf *cnf, const hp_rbm *rbm, const hp
                 n_slices += (fd[f].n + kWave - 1) / kWave + 1;   // one more offset than slices
             }
         ell_slice.assign(n_slices, 0);
-        ell_deg.assign((size_t)n_slices * kWave, 0);
+        ell_deg.assign((size_t)n_slices * kWave * 2, 0);
         each_formula([&](int f) {
             if (kind[f] != kBucketPull) return;
-            uint32_t *deg = ell_deg.data() + fd[f].slice_off * kWave;
+            uint32_t *deg = ell_deg.data() + fd[f].slice_off * kWave * 2;
             const int64_t c0 = fd[f].clause_off, c1 = c0 + fd[f].c;
             for (int k = 0; k < K; ++k)
-                for (int64_t c = c0; c < c1; ++c) deg[lits[(size_t)k * NC + c] & 0x7fff]++;
+                for (int64_t c = c0; c < c1; ++c) deg[2 * (lits[(size_t)k * NC + c] & 0x7fff)]++;
             const int sl = (fd[f].n + kWave - 1) / kWave;
             for (int j = 0; j < sl; ++j) {
-                const uint32_t w = *std::max_element(deg + j * kWave, deg + (j + 1) * kWave);
-                ell_slice[fd[f].slice_off + j] = std::max(4u, (w + 3) / 4 * 4);
+                uint64_t sum = 0;
+                for (int i = j * kWave; i < (j + 1) * kWave; ++i) sum += deg[2 * i];
+                const uint64_t most = std::max<uint64_t>(16, 4 * sum / kWave);
+                uint32_t width = 4;
+                for (int i = j * kWave; i < (j + 1) * kWave; ++i) {
+                    if (deg[2 * i] > most) deg[2 * i] |= 0x80000000u;     // (K C_f < 2^31)
+                    else width = std::max(width, (deg[2 * i] + 3) / 4 * 4);
+                }
+                ell_slice[fd[f].slice_off + j] = width;
             }
         });
-        uint64_t pos = 0;                      // widths to offsets
+        // the lists by themselves first (their words below K NC < 2^32), then the
+        // slices: widths to offsets (in 64 words)
+        uint64_t pos = 0;
+        for (size_t i = 0; i < ell_deg.size(); i += 2)
+            if (ell_deg[i] >> 31) {
+                ell_deg[i + 1] = (uint32_t)pos;
+                pos += ell_deg[i] & 0x7fffffffu;
+            }
+        pos = (pos + kWave - 1) / kWave;
         for (uint32_t &w : ell_slice) {
             const uint32_t width = w;
             w = (uint32_t)pos;
             pos += width;
         }
-        if (pos >= (uint64_t(1) << 32)) {
-            release(p);
-            return fail(HP_EUNSUPPORTED, "too many clause slots");
-        }
-        try {                                  // 64 words per entry of a slice's longest list
-            ell.assign((size_t)pos * kWave, 0);
-        } catch (const std::bad_alloc &) {
-            release(p);
-            return fail(HP_ENOMEM, "host allocation failed");
-        }
+        ell.assign((size_t)pos * kWave, 0);
         each_formula([&](int f) {
             if (kind[f] != kBucketPull) return;
             const uint32_t *first = ell_slice.data() + fd[f].slice_off;
-            std::vector<uint32_t> fill(fd[f].n, 0);
+            uint32_t *deg = ell_deg.data() + fd[f].slice_off * kWave * 2;
+            for (int i = 0; i < fd[f].n; ++i) deg[2 * i] &= 0x80000000u;  // counted again as the lists fill
             const int64_t c0 = fd[f].clause_off, c1 = c0 + fd[f].c;
             for (int64_t c = c0; c < c1; ++c)
                 for (int k = 0; k < K; ++k) {
                     const uint16_t e = lits[(size_t)k * NC + c];
-                    const uint32_t i = e & 0x7fffu;
-                    ell[((size_t)first[i / kWave] + fill[i]++) * kWave + i % kWave] =
-                        ((uint32_t)(c - c0) << 4) | ((uint32_t)(e >> 15) << 3) | (uint32_t)k;
+                    const uint32_t i = e & 0x7fffu, j = deg[2 * i]++;
+                    const size_t at = j >> 31 ? (size_t)deg[2 * i + 1] + (j & 0x7fffffffu)
+                                              : ((size_t)first[i / kWave] + j) * kWave + i % kWave;
+                    ell[at] = ((uint32_t)(c - c0) << 4) | ((uint32_t)(e >> 15) << 3) | (uint32_t)k;
                 }
         });
+    } catch (const std::bad_alloc &) {
+        release(p);
+        return fail(HP_ENOMEM, "host allocation failed");
     }
     // Buckets: one per size class of the push family (the formulas of a class
     // share a launch whatever table layout each would fit, so the chains of

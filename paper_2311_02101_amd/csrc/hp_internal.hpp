@@ -133,11 +133,12 @@ template <typename Real>
 struct SweepParams {
     const FormulaDev *fd;
     const WorkItem *work;
-    // pull: occurrence lists of 64 consecutive variables (a slice) interleaved,
-    // [slice entry][64] words (c_local << 4) | (negated << 3) | k in ascending
-    // (c, k), padded with zeros to a multiple of 4 entries; slice offsets (in
-    // entries, from FormulaDev::slice_off) and the variables' list lengths
-    // ([slice][64], from 64 slice_off)
+    // pull: occurrence lists, words (c_local << 4) | (negated << 3) | k in
+    // ascending (c, k): long ones by themselves, then those of 64 consecutive
+    // variables (a slice) interleaved, [slice entry][64], padded with zeros to a
+    // multiple of 4 entries; slice offsets (in entries, from
+    // FormulaDev::slice_off); per variable its list's length and, for a list by
+    // itself, bit 31 and the list's first word ([slice][64][2], from 128 slice_off)
     const uint32_t *ell, *ell_slice, *ell_deg;
     const uint4 *rec;            // push: clause records [ctot]
     const uint32_t *orig;        // push: first Philox block of the record's hidden draw [ctot]

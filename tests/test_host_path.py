@@ -29,3 +29,26 @@ for name in ("hp_run", "hp_run_noalloc"):
     assert got["ok"] == 0 and got["t"] == 7
     assert got["hp_run"] == [-3, 7, 0, 8]
     assert got["hp_run_noalloc"] == [-3, 8, 0, 9]
+
+
+# A variable in every clause must not pad its neighbours' lists to its own
+# length: pull formulas with such variables cost the device memory of their
+# occurrences (four times at most, here with one in every slice of 64 variables)
+@pytest.mark.parametrize("every", [0, 1, 64])
+def test_device_memory_of_pull_lists(tmp_path, every):
+    got = run(tmp_path, f"""
+n, c, k = 4096, 20000, 3
+rng = np.random.default_rng(1)
+T = rng.integers(1, n + 1, (k, c)).astype(np.int32)
+hubs = 1 if {every} == 1 else n // 64
+if {every}:
+    T[1] = rng.integers(0, hubs, c) * 64 + 1
+W, b, _ = wl.pretrained_rbm(k, wl.FSTAR_PAIR)
+free = stub.stub_bytes()
+p = Plan([T], [n], W, b, chains=2, kernel="pull")
+pull = stub.stub_bytes() - free
+q = Plan([T], [n], W, b, chains=2, kernel="push", split=1)
+out = dict(pull=pull, push=stub.stub_bytes() - free - pull, occurrences=k * c, n=n)
+""")
+    lists = got["pull"] - got["push"]
+    assert lists <= 4 * (4 * got["occurrences"] + 20 * got["n"])
