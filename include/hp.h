@@ -94,7 +94,10 @@ typedef struct {
     int32_t precision;              /* hp_precision                                    */
     double alpha;                   /* variance moving-average rate, in [0, 1]         */
     uint64_t seed;                  /* Philox key source                               */
-    int32_t threads;                /* workgroup size override (0 = automatic)         */
+    int32_t threads;                /* workgroup size override (0 = automatic); with
+                                       HP_KERNEL_PUSH it also keeps every table in LDS
+                                       where they fit, which is otherwise the automatic
+                                       choice's and hp_tune's to decide              */
     int32_t split;                  /* workgroups per chain of the push kernel: 0 =
                                        automatic (up to filling the device, where the
                                        exchange pays), 1 = one, or a power of two up

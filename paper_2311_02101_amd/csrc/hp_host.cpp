@@ -121,7 +121,8 @@ int vpt_for(const Bucket &bk, int threads, int cus, bool mixed, bool fp64) {
 //  * layout: contribution rows read from global memory (wide) wherever all
 //    tables would fit in LDS too: the rows of two temperatures (64 KB) stay in
 //    the caches, their reads leave the LDS pipe to gathers and accumulators,
-//    and less LDS admits more workgroups per CU.  Same 1024 threads, 256
+//    and less LDS admits more workgroups per CU (a caller that names both
+//    the push kernel and its workgroup size keeps them in LDS).  Same 1024 threads, 256
 //    chains: 2000 variables 15.7 -> 13.9, 8000 56 -> 47; with the workgroups it
 //    admits, 4160 chains of 1000 variables 135 -> 94.
 //  * one chain per CU or fewer: as many threads as clauses, up to 1024 (64
@@ -138,8 +139,8 @@ int vpt_for(const Bucket &bk, int threads, int cus, bool mixed, bool fp64) {
 //  * steps from the counter where nothing else fills the CU at the barrier
 //    (four steps per wave up), or from sixty steps per wave up; else
 //    round-robin (512 variables, 1088 chains, FP64 21.4 -> 19.7).
-void default_shape(const Plan &p, Bucket &bk, int threads, int max_lds, bool clust, bool fp64) {
-    if (!clust && bk.kind == kBucketPush) bk.kind = kBucketWide;
+void default_shape(const Plan &p, Bucket &bk, int threads, int max_lds, bool clust, bool fp64, bool push_named) {
+    if (!clust && bk.kind == kBucketPush && !(push_named && threads != 0)) bk.kind = kBucketWide;
     bk.lds = clust ? lds_bytes_clust(bk.max_n, &bk.v_off, &bk.x_off)
                    : lds_bytes_push(bk.max_n, bk.kind, &bk.v_off, &bk.x_off);
     if (threads == 0) {
@@ -706,7 +707,8 @@ hp_status hp_plan(hp_plan_t *out, const hp_cnf *cnf, const hp_rbm *rbm, const hp
             bk.threads = t;
             bk.vpt = vpt_for(bk, t, p->cus, mixed, opts->precision != HP_FP32);
         } else {
-            default_shape(*p, bk, opts->threads, max_lds, clust, opts->precision != HP_FP32);
+            default_shape(*p, bk, opts->threads, max_lds, clust, opts->precision != HP_FP32,
+                          opts->kernel == HP_KERNEL_PUSH);
         }
         // persistent grid when the items outnumber the resident workgroups
         const int occ = bucket_occupancy(*p, bk);
