@@ -35,3 +35,26 @@ def test_every_step_once_and_numbers_per_sweep(T, W):
         for s in range(6):
             assert sorted(run_sweep(T, W, counter, s * (T // 2), rng)) == list(range(T))
             assert counter[0] == (s + 1) * (T // 2)
+
+
+def test_no_steps():
+    """A split member without records: nothing taken, no number consumed."""
+    counter = [0]
+    for s in range(3):
+        assert run_sweep(0, 16, counter, 0, random.Random(s)) == []
+    assert counter == [0]
+
+
+@pytest.mark.parametrize("T,W", [(28, 4), (31, 4), (33, 16), (40, 16)])
+@pytest.mark.parametrize("off", [-1, 1])
+def test_another_count_per_sweep_is_caught(T, W, off):
+    """One number more or less a sweep repeats or skips steps from the second on
+    (where the counter hands out any)."""
+    counter, rng = [0], random.Random(T)
+    right = []
+    for s in range(4):
+        try:
+            right.append(sorted(run_sweep(T, W, counter, s * (T // 2 + off), rng)) == list(range(T)))
+        except IndexError:
+            right.append(False)
+    assert right[0] and not all(right[1:])
