@@ -121,8 +121,7 @@ int vpt_for(const Bucket &bk, int threads, int cus, bool mixed, bool fp64) {
 //  * layout: contribution rows read from global memory (wide) wherever all
 //    tables would fit in LDS too: the rows of two temperatures (64 KB) stay in
 //    the caches, their reads leave the LDS pipe to gathers and accumulators,
-//    and less LDS admits more workgroups per CU (a caller that names both
-//    the push kernel and its workgroup size keeps them in LDS).  Same 1024 threads, 256
+//    and less LDS admits more workgroups per CU.  Same 1024 threads, 256
 //    chains: 2000 variables 15.7 -> 13.9, 8000 56 -> 47; with the workgroups it
 //    admits, 4160 chains of 1000 variables 135 -> 94.
 //  * one chain per CU or fewer: as many threads as clauses, up to 1024 (64
@@ -139,12 +138,35 @@ int vpt_for(const Bucket &bk, int threads, int cus, bool mixed, bool fp64) {
 //  * steps from the counter where nothing else fills the CU at the barrier
 //    (four steps per wave up), or from sixty steps per wave up; else
 //    round-robin (512 variables, 1088 chains, FP64 21.4 -> 19.7).
+// A workgroup size that the caller gives is kept.  Its waves may be few, and then
+// nothing hides the latency of a read from the caches or of the step counter:
+//  * layout: wide only if it lets more workgroups share a CU, or from 1024
+//    resident threads up (rows in LDS / wide, 256 threads: 500 variables x 256
+//    chains 8.8 / 9.4, x 2500 46.7 / 42.0; 1024 threads: 8000 x 256 58.6 / 53.7);
+//    with the push kernel named too, all tables in LDS where they fit;
+//  * steps from the counter for 1024 threads only (counter / round-robin, 8000
+//    variables x 16 chains: 256 threads 110.6 / 100.7, 512 65.6 / 64.2, 1024
+//    51.3 / 53.2).
 void default_shape(const Plan &p, Bucket &bk, int threads, int max_lds, bool clust, bool fp64, bool push_named) {
-    if (!clust && bk.kind == kBucketPush && !(push_named && threads != 0)) bk.kind = kBucketWide;
-    bk.lds = clust ? lds_bytes_clust(bk.max_n, &bk.v_off, &bk.x_off)
-                   : lds_bytes_push(bk.max_n, bk.kind, &bk.v_off, &bk.x_off);
-    if (threads == 0) {
-        const int m = (bk.count + p.cus - 1) / p.cus;                  // chains per CU
+    const bool given = threads != 0;
+    auto layout = [&](int kind) {
+        bk.kind = kind;
+        bk.lds = clust ? lds_bytes_clust(bk.max_n, &bk.v_off, &bk.x_off)
+                       : lds_bytes_push(bk.max_n, bk.kind, &bk.v_off, &bk.x_off);
+    };
+    layout(!clust && bk.kind == kBucketPush && !given ? (int)kBucketWide : bk.kind);
+    const int m = (bk.count + p.cus - 1) / p.cus;                      // chains per CU
+    if (given && !clust && bk.kind == kBucketPush && !push_named) {
+        bk.threads = threads;
+        auto resident = [&](int kind) {
+            layout(kind);
+            bk.vpt = vpt_for(bk, threads, p.cus, false, fp64);
+            return std::min(m, std::max(1, bucket_occupancy(p, bk)));
+        };
+        const int in_lds = resident(kBucketPush), wide = resident(kBucketWide);
+        if (wide <= in_lds && in_lds * threads < 1024) layout(kBucketPush);
+    }
+    if (!given) {
         const int r = std::max(1, (int)((size_t)max_lds / bk.lds));    // workgroups per CU that LDS admits
         const int res = fp64 && bk.max_c < 3000 ? 1280 : 1536;
         const int top = fp64 && r > 3 ? 256 : 512;
@@ -160,7 +182,8 @@ void default_shape(const Plan &p, Bucket &bk, int threads, int max_lds, bool clu
     bk.threads = threads;
     bk.vpt = vpt_for(bk, threads, p.cus, false, fp64);
     const bool alone = bk.count <= p.cus || 2 * bk.lds > (size_t)max_lds || threads == kMaxThreads;
-    bk.dyn = clust || bk.max_c >= (alone ? 4 : 60) * threads ? 1 : 0;
+    if (given) bk.dyn = threads == kMaxThreads && (clust || bk.max_c >= 4 * threads) ? 1 : 0;
+    else bk.dyn = clust || bk.max_c >= (alone ? 4 : 60) * threads ? 1 : 0;
 }
 
 // Split a column of 8 weights into kLimbs BF16 limbs on the column's common
@@ -736,7 +759,8 @@ hp_status hp_plan(hp_plan_t *out, const hp_cnf *cnf, const hp_rbm *rbm, const hp
         const Bucket saved = bk;
         if (opts->threads == 0) bk.threads = kMaxThreads;
         if (!clust) {
-            bk.kind = kBucketWide;        // the split kernel's table layout
+            // the split kernel's table layout: rows in LDS for few waves of the caller's choice
+            bk.kind = !large && bk.threads < kMaxThreads ? kBucketPush : kBucketWide;
             bk.lds = lds_bytes_push(bk.max_n, bk.kind, &bk.v_off, &bk.x_off);
         }
         // resident workgroups of the variant a split of G members launches (for
@@ -788,19 +812,30 @@ hp_status hp_plan(hp_plan_t *out, const hp_cnf *cnf, const hp_rbm *rbm, const hp
             // they are few or have much to do each (8 / 16 members: 4096 x 16
             // 7.9 / 8.5, 8192 x 16 11.3 / 12.1, 8192 x 3 11.2 / 10.2).
             const double work_c = bk.max_c * (clust || L > 4 ? 1.0 : 0.6);
+            // A caller's own workgroup size keeps the rule without these lines: smaller
+            // members have more to gain (451 variables x 2 chains, 256 threads,
+            // 1 / 2 members 7.36 / 6.82; 7583 x 12, 8 / 16 30.0 / 21.7).
+            const bool given = opts->threads != 0;
             auto pays = [&](int g) {
+                if (given) return bk.max_c / g >= 1024;
                 return work_c >= 3000 && bk.max_c / g >= 1024 &&
                        (g < 16 || (int64_t)n_items * g * 2 <= p->cus || bk.max_c / g >= 6144);
             };
             while (G * 2 <= kMaxSplit && G * 2 <= min_groups && (int64_t)n_items * G * 2 <= capacity(G * 2) &&
                    pays(G * 2) && scratch_fits(G * 2) && !(large && saved.grid))
                 G *= 2;
-            if (G == 2 && work_c < 4096) G = 1;
+            if (G == 2 && work_c < 4096 && !given) G = 1;
         }
         if (G == 1) bk = saved;           // no split: keep the bucket's own shape
         else bk.grid = 0;                 // split launches run one item per group
         p->solo = G > 1 && large ? 1 : 0;
-        p->solo_bucket = saved;
+        if (p->solo) {
+            Bucket &sb = p->solo_bucket;
+            sb = saved;
+            sb.kind = kBucketWide;
+            sb.lds = lds_bytes_push(sb.max_n, sb.kind, &sb.v_off, &sb.x_off);
+            sb.vpt = 0;
+        }
     }
     p->split = G;
     p->wait_limit = opts->split_wait_limit;

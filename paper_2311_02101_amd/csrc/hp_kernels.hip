@@ -1597,14 +1597,19 @@ __device__ __forceinline__ bool join_members(uint32_t *word, uint32_t G, uint32_
 // the caches), which takes a read per literal off the LDS pipe that the
 // gathers, the threshold rows and the accumulator updates already fill.
 // 4096 variables x 64 chains, FP64: 4.93 -> 4.77 ms per 500 sweeps.
-template <bool kClust>
-constexpr int kSplitTab = kClust ? kBucketPush : kBucketWide;
+// kFew: a workgroup size below 1024 that the caller gave; its few waves do not
+// hide the latency of those reads, nor of the step counter, so the rows are in LDS
+// and the steps dealt round-robin (us per sweep, as the others / so: 4096 variables x
+// 16 chains, 16 members of 256 threads 11.4 / 11.0, 2000 x 32, 8 of 512 7.7 / 6.3, 1027
+// x 8, 4 of 64 25.9 / 22.8).
+template <bool kClust, bool kFew>
+constexpr int kSplitTab = kClust || kFew ? kBucketPush : kBucketWide;
 
-template <typename Real, int VPT, bool kClust, bool kSample, int NB>
+template <typename Real, int VPT, bool kClust, bool kFew, bool kSample, int NB>
 __device__ __forceinline__ void split_sweeps(const SweepParams<Real> &P, const SplitParams &Q, const SplitCtx<Real> &c,
                                              Real (&nu)[VPT > 0 ? VPT : 1], const int32_t (&ncr)[VPT > 0 ? VPT : 1],
                                              int &smax) {
-    constexpr int kTab = kSplitTab<kClust>;
+    constexpr int kTab = kSplitTab<kClust, kFew>;
     const PushLds &L = c.L;
     const int G = c.G, g = c.g, N = c.N, tid = c.tid, NT = c.NT;
     const int own_lo = c.q_lo * 4, own_hi = min(N, c.q_hi * 4);
@@ -1612,7 +1617,7 @@ __device__ __forceinline__ void split_sweeps(const SweepParams<Real> &P, const S
     const int lane = tid & (kWave - 1);
     const RecView rv = rec_view(c.rec + c.c_lo, c.orig + c.c_lo, c.c_hi - c.c_lo);
     auto step_counter = [&](int64_t s) {
-        return StepCounter{(int)s * c.steps, 1, __builtin_amdgcn_readfirstlane(tid / kWave), NT / kWave};
+        return StepCounter{(int)s * c.steps, kFew ? 0 : 1, __builtin_amdgcn_readfirstlane(tid / kWave), NT / kWave};
     };
     StepPipe pipe = start_pipe(rv, c.bnd, step_counter(0), lane);
     for (int64_t s = 0; s < c.S; ++s) {
@@ -1737,7 +1742,7 @@ __device__ __forceinline__ void split_sweeps(const SweepParams<Real> &P, const S
 }
 
 // kJoin: the members of an item get together first (Plan::solo).
-template <typename Real, int VPT, bool kClust = false, bool kJoin = false>
+template <typename Real, int VPT, bool kClust = false, bool kJoin = false, bool kFew = false>
 __global__ __launch_bounds__(1024) void sweep_split_kernel(SweepParams<Real> P, SplitParams Q) {
     extern __shared__ __align__(16) unsigned char lds[];
     SplitCtx<Real> c;
@@ -1770,7 +1775,7 @@ __global__ __launch_bounds__(1024) void sweep_split_kernel(SweepParams<Real> P, 
     const FormulaDev fd = P.fd[w.f];
     const int N = fd.n;
     const int tau = P.temp_of_chain[(int64_t)w.f * P.B + w.b];
-    c.L = kClust ? push_lds_clust(lds, P.lds_x_off) : push_lds_for<kSplitTab<kClust>>(lds, P.lds_x_off, P.gfx, tau);
+    c.L = kClust ? push_lds_clust(lds, P.lds_x_off) : push_lds_for<kSplitTab<kClust, kFew>>(lds, P.lds_x_off, P.gfx, tau);
     const PushLds &L = c.L;
     c.G = G;
     c.g = g;
@@ -1805,7 +1810,7 @@ __global__ __launch_bounds__(1024) void sweep_split_kernel(SweepParams<Real> P, 
     c.vbuf = reinterpret_cast<uint32_t *>(Q.vbuf + (size_t)item * Q.nstride);
     c.pcnt = Q.cnt + (size_t)item * 2 * kMaxSplit;
 
-    load_push_tables<kSplitTab<kClust>, kClust>(L, P.thr, P.gfx, P.gpad, tau, tid, NT, (1u << P.K) - 1u);
+    load_push_tables<kSplitTab<kClust, kFew>, kClust>(L, P.thr, P.gfx, P.gpad, tau, tid, NT, (1u << P.K) - 1u);
     for (int i = tid; i < N; i += NT) {
         L.v[i] = P.v[c.sbase + i];
         L.x[i] = 0;
@@ -1827,11 +1832,11 @@ __global__ __launch_bounds__(1024) void sweep_split_kernel(SweepParams<Real> P, 
     __syncthreads();
 
     if (P.n_sweeps <= 0)
-        split_sweeps<Real, VPT, kClust, false, kClust ? 0 : 2>(P, Q, c, nu, ncr, smax);
+        split_sweeps<Real, VPT, kClust, kFew, false, kClust ? 0 : 2>(P, Q, c, nu, ncr, smax);
     else if (kClust || c.nbh > 1)
-        split_sweeps<Real, VPT, kClust, true, kClust ? 0 : 2>(P, Q, c, nu, ncr, smax);
+        split_sweeps<Real, VPT, kClust, kFew, true, kClust ? 0 : 2>(P, Q, c, nu, ncr, smax);
     else
-        split_sweeps<Real, VPT, kClust, true, kClust ? 0 : 1>(P, Q, c, nu, ncr, smax);
+        split_sweeps<Real, VPT, kClust, kFew, true, kClust ? 0 : 1>(P, Q, c, nu, ncr, smax);
 
     // write back the owned part of the state
     for (int i = own_lo + tid; i < own_hi; i += NT) P.v[c.sbase + i] = L.v[i];
@@ -1954,7 +1959,11 @@ const void *clust_kernel_ptr(int vpt) {
 
 // owned variables per thread of a split member: 1 or 2 in registers, else 0
 template <typename Real>
-const void *split_kernel_ptr(bool clust, int vpt, bool join = false) {
+const void *split_kernel_ptr(bool clust, int vpt, bool join = false, bool few = false) {
+    if (few)
+        return vpt == 1 ? (const void *)sweep_split_kernel<Real, 1, false, false, true>
+               : vpt == 2 ? (const void *)sweep_split_kernel<Real, 2, false, false, true>
+                          : (const void *)sweep_split_kernel<Real, 0, false, false, true>;
     if (join)
         return vpt == 1 ? (const void *)sweep_split_kernel<Real, 1, false, true>
                : vpt == 2 ? (const void *)sweep_split_kernel<Real, 2, false, true>
@@ -1968,16 +1977,10 @@ const void *split_kernel_ptr(bool clust, int vpt, bool join = false) {
                       : (const void *)sweep_split_kernel<Real, 0>;
 }
 
-// formulas above 13 600 variables hold the averages of 4 groups in FP32 on 1024
-// threads, else none
+// the launch behind a joined split: one form (Plan::solo_bucket), it hardly ever runs
 template <typename Real>
-const void *solo_kernel_ptr(int vpt, int kind) {
-    constexpr int V = sizeof(Real) == 4 ? 4 : 0;
-    if (kind == kBucketMid)
-        return vpt == V ? (const void *)sweep_push_kernel<Real, V, kBucketMid, false, false, true>
-                        : (const void *)sweep_push_kernel<Real, 0, kBucketMid, false, false, true>;
-    return vpt == V ? (const void *)sweep_push_kernel<Real, V, kBucketWide, false, false, true>
-                    : (const void *)sweep_push_kernel<Real, 0, kBucketWide, false, false, true>;
+const void *solo_kernel_ptr() {
+    return (const void *)sweep_push_kernel<Real, 0, kBucketWide, false, false, true>;
 }
 
 const void *mixed_kernel_ptr(int vpt) {
@@ -2005,9 +2008,9 @@ hipError_t set_limits_t(int bytes) {
         ks.push_back(split_kernel_ptr<Real>(false, vpt));
         ks.push_back(split_kernel_ptr<Real>(true, vpt));
         ks.push_back(split_kernel_ptr<Real>(false, vpt, true));
+        ks.push_back(split_kernel_ptr<Real>(false, vpt, false, true));
     }
-    for (int vpt : {0, 4})
-        for (int kind : {(int)kBucketWide, (int)kBucketMid}) ks.push_back(solo_kernel_ptr<Real>(vpt, kind));
+    ks.push_back(solo_kernel_ptr<Real>());
     for (const void *k : ks) {
         hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
         if (e != hipSuccess) return e;
@@ -2048,8 +2051,9 @@ int split_occupancy(const Plan &p, int G) {
     int nb = 0;
     const Bucket &b = p.buckets[0];
     const int vpt = split_vpt(b.max_n, G, b.threads);
-    const void *kern = p.precision == HP_FP64 ? split_kernel_ptr<double>(p.clust, vpt)
-                                              : split_kernel_ptr<float>(p.clust, vpt);
+    const bool few = !p.clust && b.kind == kBucketPush;
+    const void *kern = p.precision == HP_FP64 ? split_kernel_ptr<double>(p.clust, vpt, false, few)
+                                              : split_kernel_ptr<float>(p.clust, vpt, false, few);
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, b.threads, b.lds) != hipSuccess) return 0;
     return nb;
 }
@@ -2060,7 +2064,7 @@ hipError_t launch_split_one(const Plan &p, SweepParams<Real> P, SplitParams Q, i
     // The plan checked that all count*G workgroups fit on the device at once
     // (occupancy x CUs), so on an otherwise idle device they are all resident
     // together; the waits for the other members are bounded either way (see hp_check).
-    hipLaunchKernelGGL((void (*)(SweepParams<Real>, SplitParams))split_kernel_ptr<Real>(p.clust, vpt, p.solo),
+    hipLaunchKernelGGL((void (*)(SweepParams<Real>, SplitParams))split_kernel_ptr<Real>(p.clust, vpt, p.solo, !p.clust && b.kind == kBucketPush),
                        dim3(b.count * p.split), dim3(b.threads), b.lds, s, P, Q);
     return hipGetLastError();
 }
@@ -2200,7 +2204,7 @@ hipError_t launch_bucket_t(const Plan &p, const Bucket &b, const hp_state &st, i
         Q.ctr = queues + kQueueWords * (size_t)(&b - p.buckets.data());
         grid = b.grid;
     }
-    const void *kern = join                          ? solo_kernel_ptr<Real>(b.vpt, b.kind)
+    const void *kern = join                          ? solo_kernel_ptr<Real>()
                        : p.precision == HP_MIXED_BF16 ? mixed_kernel_ptr(b.vpt)
                        : p.clust                     ? clust_kernel_ptr<Real>(b.vpt)
                                                      : push_kernel_ptr<Real>(b.vpt, b.kind);
