@@ -72,9 +72,18 @@ __global__ __launch_bounds__(kPackThreads) void pack_kernel(const FormulaDev *__
 // planes: 31 us for both sets of the same batch (2 x 54 M clause tests), before
 // 710 us with one chain per workgroup and a byte gather from global memory per
 // literal.
+// Fewer than 512 threads for small formulas, about eight clauses each (3000
+// formulas of 60 clauses x 8 chains, the whole merge: 86 us with one chain per
+// workgroup, 127 with 512 threads here and 16 slabs of columns below, 31 so).
 constexpr int kCountThreads = 512;
 constexpr int kPlanes = 5;
 static_assert(kTileClauses / kCountThreads < (1 << kPlanes), "a lane's clauses fit its counter planes");
+
+static int count_threads(int max_c) {
+    int t = kWave;
+    while (t < kCountThreads && t * 8 < max_c) t *= 2;
+    return t;
+}
 
 __global__ __launch_bounds__(kCountThreads) void count_kernel(const FormulaDev *__restrict__ fd,
                                                               const ClauseTile *__restrict__ tile,
@@ -85,16 +94,16 @@ __global__ __launch_bounds__(kCountThreads) void count_kernel(const FormulaDev *
     __shared__ int32_t s_cnt[32];
     const ClauseTile t = tile[blockIdx.x];
     const FormulaDev &f = fd[t.f];
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), g = (int)blockIdx.y;
+    const int tid = threadIdx.x, NT = blockDim.x, lane = tid & (kWave - 1), g = (int)blockIdx.y;
     const uint32_t *src = bits + ((int64_t)blockIdx.z * gridDim.y + g) * nv + f.var_off;
-    for (int i = tid; i < f.n; i += kCountThreads) s_w[i] = src[i];
+    for (int i = tid; i < f.n; i += NT) s_w[i] = src[i];
     if (tid < 32) s_cnt[tid] = 0;
     __syncthreads();
     const uint4 *__restrict__ r = rec + f.clause_off;
     const int c_hi = min(f.c, t.c0 + kTileClauses);
     uint32_t pl[kPlanes] = {};
 #pragma unroll 2
-    for (int c = t.c0 + tid; c < c_hi; c += kCountThreads) {
+    for (int c = t.c0 + tid; c < c_hi; c += NT) {
         const uint4 q = r[c];
         const uint32_t len = rec_len(q.w);
         const uint32_t e[7] = {q.x & 0xffffu, q.x >> 16, q.y & 0xffffu, q.y >> 16,
@@ -143,10 +152,10 @@ __global__ void select_kernel(const int32_t *__restrict__ cnt_cur, const int32_t
 #pragma unroll 8
             for (int k = 0; k < 2 * B; ++k) rank += (s_c[k] < cj || (s_c[k] == cj && k < j)) ? 1 : 0;
         } else {
-            for (int k = 0; k < 2 * B; ++k) {
-                const int32_t ck = k < B ? a[k] : r[k - B];
-                rank += (ck < cj || (ck == cj && k < j)) ? 1 : 0;
-            }
+#pragma unroll 8
+            for (int k = 0; k < B; ++k) rank += (a[k] < cj || (a[k] == cj && k < j)) ? 1 : 0;
+#pragma unroll 8
+            for (int k = 0; k < B; ++k) rank += (r[k] < cj || (r[k] == cj && k + B < j)) ? 1 : 0;
         }
         if (rank >= B) src[(int64_t)f * B + (rank - B)] = j;
     }
@@ -242,12 +251,12 @@ hipError_t launch_merge(Plan &p, const hp_state &st, const uint8_t *cand, hipStr
     int32_t *cnt_cur = p.d_mg_cnt, *cnt_ret = p.d_mg_cnt + items, *src = p.d_mg_cnt + 2 * items;
     pack_kernel<<<dim3(p.n_tiles, groups, 2), kPackThreads, 0, s>>>(p.d_fd, p.d_tile, p.B, p.total_vars, st.v, cand,
                                                                    p.d_mg_bits, p.d_mg_cnt, (int64_t)(2 * items));
-    count_kernel<<<dim3(p.n_ctiles, groups, 2), kCountThreads, lds, s>>>(p.d_fd, p.d_ctile, p.d_rec, p.B, p.total_vars,
-                                                                         p.d_mg_bits, (int64_t)items, p.d_mg_cnt);
+    count_kernel<<<dim3(p.n_ctiles, groups, 2), count_threads(p.max_c), lds, s>>>(
+        p.d_fd, p.d_ctile, p.d_rec, p.B, p.total_vars, p.d_mg_bits, (int64_t)items, p.d_mg_cnt);
     select_kernel<<<p.F, 256, 0, s>>>(cnt_cur, cnt_ret, p.B, src);
     if (in_place) {
         const int waves = std::min(kPermWaves, (p.B + kPermRows - 1) / kPermRows * 2);
-        const dim3 grid(p.n_tiles, kTileVars / kWave);
+        const dim3 grid(p.n_tiles, (std::min(p.max_n, kTileVars) + kWave - 1) / kWave);
         if (st.nu_bytes == 4)
             permute_rows_kernel<float><<<grid, waves * kWave, 0, s>>>(p.d_fd, p.d_tile, p.B, src, st.v, cand,
                                                                       reinterpret_cast<float *>(st.nu));

@@ -75,7 +75,9 @@ __global__ void fe_table_clust_kernel(ClustRbm R, int T, double *__restrict__ fe
 // Bound by the latency of a clause's dependent record, LDS gather and table
 // reads: 32 chains of 12 288 clauses at 16 temperatures take 4.6 us, before
 // 100 us with one workgroup of 256 threads per chain, gathers from global
-// memory and all 16 columns.
+// memory and all 16 columns.  Small formulas take fewer threads, at least one
+// clause each (3000 formulas of 60 clauses x 8 chains, the whole round: 48 us with 256
+// threads each, 74 with 512, 21 so).
 template <bool kClust>
 __global__ __launch_bounds__(kFeThreads) void free_energy_kernel(const FormulaDev *__restrict__ fd,
                                                                  const WorkItem *__restrict__ work,
@@ -94,11 +96,11 @@ __global__ __launch_bounds__(kFeThreads) void free_energy_kernel(const FormulaDe
     const int lo = tau - ((tau - parity) & 1);            // lower temperature of the pair
     if (lo < parity || lo + 1 >= T) return;
     const FormulaDev &f = fd[w.f];
-    const int n = f.n, tid = threadIdx.x;
+    const int n = f.n, tid = threadIdx.x, NT = blockDim.x;
     const uint8_t *vb = v + f.var_off * B + (int64_t)w.b * n;
-    for (int i = tid; i < kRows; i += kFeThreads)
+    for (int i = tid; i < kRows; i += NT)
         s_fe[i] = make_double2(fe[lo * kRows + i], fe[(lo + 1) * kRows + i]);
-    for (int i = 4 * tid; i < n; i += 4 * kFeThreads) {
+    for (int i = 4 * tid; i < n; i += 4 * NT) {
         uint32_t x = 0;
         if (i + 4 <= n) {
             __builtin_memcpy(&x, vb + i, 4);
@@ -113,7 +115,7 @@ __global__ __launch_bounds__(kFeThreads) void free_energy_kernel(const FormulaDe
     const int c_lo = (int)((int64_t)f.c * part / parts), c_hi = (int)((int64_t)f.c * (part + 1) / parts);
     double a0 = 0.0, a1 = 0.0;
 #pragma unroll 2
-    for (int c = c_lo + tid; c < c_hi; c += kFeThreads) {
+    for (int c = c_lo + tid; c < c_hi; c += NT) {
         const uint4 q = r[c];
         const uint32_t len = rec_len(q.w), negm = rec_negm(q.w);
         const uint32_t e[7] = {q.x & 0xffffu, q.x >> 16, q.y & 0xffffu, q.y >> 16,
@@ -144,7 +146,7 @@ __global__ __launch_bounds__(kFeThreads) void free_energy_kernel(const FormulaDe
     __syncthreads();
     if (tid == 0) {
         double2 t = s_part[0];
-        for (int i = 1; i < kFeThreads / kWave; ++i) {
+        for (int i = 1; i < NT / kWave; ++i) {
             t.x += s_part[i].x;
             t.y += s_part[i].y;
         }
@@ -238,12 +240,14 @@ hipError_t launch_temper(Plan &p, const hp_state &st, int parity, hipStream_t s)
     while (parts < kFeParts && items * parts * 2 <= (size_t)p.cus * 2 && p.max_c / (parts * 2) >= 2 * kFeThreads)
         parts *= 2;
     const dim3 grid((unsigned)items, (unsigned)parts);
+    int threads = kFeThreads;
+    while (threads > kWave && threads / 2 >= p.max_c) threads /= 2;
     const size_t lds = ((size_t)p.max_n + 15) / 16 * 16;
     if (p.clust)
-        free_energy_kernel<true><<<grid, kFeThreads, lds, s>>>(p.d_fd, p.d_work_fb, p.d_rec, p.B, p.T, parity, 0u,
+        free_energy_kernel<true><<<grid, threads, lds, s>>>(p.d_fd, p.d_work_fb, p.d_rec, p.B, p.T, parity, 0u,
                                                                p.d_temp, st.v, p.d_fe, p.d_fe_chain);
     else
-        free_energy_kernel<false><<<grid, kFeThreads, lds, s>>>(p.d_fd, p.d_work_fb, p.d_rec, p.B, p.T, parity,
+        free_energy_kernel<false><<<grid, threads, lds, s>>>(p.d_fd, p.d_work_fb, p.d_rec, p.B, p.T, parity,
                                                                 (1u << p.K) - 1u, p.d_temp, st.v, p.d_fe,
                                                                 p.d_fe_chain);
     swap_kernel<<<p.F, kWave, 0, s>>>(p.d_temp, p.d_fe_chain, p.B, p.T, parts, parity, st.t, p.d_temp_list,
