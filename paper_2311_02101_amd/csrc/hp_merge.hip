@@ -239,7 +239,15 @@ hipError_t launch_merge(Plan &p, const hp_state &st, const uint8_t *cand, hipStr
     const size_t items = (size_t)p.F * p.B;
     const size_t vbytes = (size_t)p.total_vars * p.B;
     const unsigned groups = (unsigned)((p.B + 31) / 32);
-    const bool in_place = p.B <= kMergeRows;
+    // in place, a workgroup writes columns of v and nu that it alone reads: the
+    // returned rows may be v itself, but not another part of the same memory
+    const uintptr_t c = reinterpret_cast<uintptr_t>(cand);
+    auto meets = [&](const void *q, size_t bytes) {
+        const uintptr_t a = reinterpret_cast<uintptr_t>(q);
+        return c < a + bytes && a < c + vbytes;
+    };
+    const bool in_place =
+        p.B <= kMergeRows && (cand == st.v || !meets(st.v, vbytes)) && !meets(st.nu, vbytes * st.nu_bytes);
     hipError_t e = hipSuccess;
     if (!p.d_mg_cnt) e = hipMalloc((void **)&p.d_mg_cnt, 3 * items * sizeof(int32_t));
     if (e == hipSuccess && !p.d_mg_bits)
