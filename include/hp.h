@@ -224,7 +224,8 @@ hp_status hp_run_noalloc(hp_plan_t plan, const hp_state *state, int64_t n_sweeps
  * of the contribution rows in global memory, or all contribution rows in
  * global memory: smaller LDS footprints let more workgroups share a CU), and
  * how a chain's waves share its clause steps (from a counter or dealt
- * round-robin).  All shapes compute the same bits.  The trial runs overwrite the state's v, nu, s_max and best
+ * round-robin).  All shapes compute the same bits.  A plan that is split
+ * keeps its shape: the call returns at once.  The trial runs overwrite the state's v, nu, s_max and best
  * without advancing t, so pass a scratch state of the right shape.
  * Synchronous.  Cached graphs are discarded. */
 hp_status hp_tune(hp_plan_t plan, const hp_state *scratch, int64_t n_sweeps, void *stream);
@@ -301,7 +302,8 @@ const char *hp_last_error(void);
 #define HP_MLP_HIDDEN 256
 /* parameter vector: W1 [32][256] | b1 [256] | w2 [256] | b2 [1] */
 #define HP_MLP_PARAMS (HP_MLP_IN * HP_MLP_HIDDEN + 2 * HP_MLP_HIDDEN + 1)
-/* rows of the backward pass's partial-sum workspace (one per workgroup) */
+/* rows of the backward pass's partial-sum workspace (one per workgroup, of
+ * which there are at most this many) */
 #define HP_MLP_PARTS 1024
 
 typedef struct {                    /* caller-owned DEVICE buffers                     */
@@ -317,7 +319,7 @@ typedef struct {                    /* caller-owned DEVICE buffers              
 
 /* Per-variable features of every formula of the plan, as bfloat16
  * [sum N_f][32] rows in variable order (layout of the counts: see the
- * kernels).  The plan allocates a small FP32 workspace on first use. */
+ * kernels).  Allocates nothing. */
 hp_status hp_features(hp_plan_t plan, uint16_t *x, void *stream);
 
 /* Refresh net->w_bf16 from net->params. */
@@ -377,8 +379,10 @@ hp_status hp_unit_propagate(const hp_cnf *cnf, int32_t formula, int32_t n_chains
  * the 2B rows (current first), sorts the counts stably in ascending order
  * and keeps the last B rows as the new state->v (equal counts favour the
  * returned rows); a kept row takes the nu of the chain it came from.
- * s_max, best and t are unchanged.  The plan allocates its staging buffers
- * on first use.  Stream-ordered; cand_v must stay valid until it is done. */
+ * s_max, best and t are unchanged.  The plan allocates its workspace on
+ * first use (above 256 chains, or if cand_v lies in the memory of v or nu
+ * without being v, on the first such call also a copy of v and nu).
+ * Stream-ordered; cand_v must stay valid until it is done. */
 hp_status hp_merge_candidates(hp_plan_t plan, const hp_state *state, const uint8_t *cand_v, void *stream);
 
 /* ---- Replica exchange across the temperatures -----------------------------

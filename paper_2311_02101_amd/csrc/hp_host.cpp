@@ -128,13 +128,22 @@ int vpt_for(const Bucket &bk, int threads, int cus, bool mixed, bool fp64) {
 //    variables 6.0 -> 2.2, 256 variables 5.1 -> 2.9: a sweep there is a chain
 //    of latencies that more waves walk side by side).
 //  * m chains per CU: the most threads that keep m workgroups resident
-//    (registers hold about 1536 threads in FP32, 1280 in FP64): 300 chains of
-//    600 variables 11.9 (1024, two rounds) -> 9.0 (512).
+//    (registers hold about 1536 threads): 300 chains of 600 variables 11.9
+//    (1024, two rounds) -> 9.0 (512).  In FP64 1280 below 3000 clauses, which are
+//    too few for 1536 (256 / 512 threads, 600 chains: 1000 clauses of 3 4.0 / 5.0,
+//    2900 9.1 / 9.2; of up to 7 1200 6.3 / 7.0, 1800 8.9 / 8.5, 3480 14.0 / 12.9).
+//    Where LDS admits three workgroups, from the third chain or below 12 000
+//    clauses (512 / 1024 threads: 4000 variables, 768 chains 75.0 / 75.3, FP64 78 /
+//    80; 512 chains 51.5 / 50.2, with 8000 clauses 20.8 / 21.8); where two, from
+//    the fourth chain in FP32 (6000 variables: 768 chains 111 / 110, 1024 152 /
+//    149, 1536 210 / 216; FP64 1024 168 / 157).  One workgroup alone fills a CU
+//    with 1024.
 //  * crowded: about 6.5 sqrt(C) threads in FP32 (128 at 64 variables, 256 at
-//    256, 512 from 1000 up), fewer in FP64, whose registers hold fewer waves:
-//    fewer idle lanes in the last step of each clause length and fewer waves
-//    per barrier against fewer workgroups in flight (2000 variables, 4160
-//    chains, FP64: 512 threads 224, 256 threads 203).
+//    256, 512 from 1000 up), fewer in FP64, whose registers hold fewer waves, and
+//    no more than 256 where LDS admits more than three workgroups: fewer idle
+//    lanes in the last step of each clause length and fewer waves per barrier
+//    against fewer workgroups in flight (2000 variables, 4160 chains, FP64: 512
+//    threads 214, 256 threads 206).
 //  * steps from the counter where nothing else fills the CU at the barrier
 //    (four steps per wave up), or from sixty steps per wave up; else
 //    round-robin (512 variables, 1088 chains, FP64 21.4 -> 19.7).
@@ -810,7 +819,9 @@ hp_status hp_plan(hp_plan_t *out, const hp_cnf *cnf, const hp_rbm *rbm, const hp
             // of 16384 x 32, two members 89.9 / 58.0, of 14000 x 16, eight 82.7 /
             // 17.6, one sweep alone 95.7 / 49.6).  Sixteen members exchange more than they save unless
             // they are few or have much to do each (8 / 16 members: 4096 x 16
-            // 7.9 / 8.5, 8192 x 16 11.3 / 12.1, 8192 x 3 11.2 / 10.2).
+            // 8.3 / 9.2, 8192 x 16 12.6 / 13.7, 8192 x 3 12.2 / 11.1; size-clustered
+            // 6000 x 8 9.4 / 9.5, but 3001 x 8 6.7 / 7.5, and 1500 x 8 has four
+            // members at 5.3, eight at 5.8: these lines were drawn in the padded model).
             const double work_c = bk.max_c * (clust || L > 4 ? 1.0 : 0.6);
             // A caller's own workgroup size keeps the rule without these lines: smaller
             // members have more to gain (451 variables x 2 chains, 256 threads,

@@ -218,7 +218,7 @@ size_t lds_bytes_pull(int max_n, int max_c, size_t real_bytes, int32_t *v_off, i
 
 // push LDS layout: thr (8 KB) | table rows (32 KB) | counts | v (1 B/var) | x (8 B/var)
 // The push kernels' threshold rows are indexed by clause length and the
-// pattern of the clause's own literals: row 2^len - 2 + m for len = 1..7
+// pattern of the clause's own literals: row 2^len + m for len = 1..7
 // holds the row of the padded pattern (m with positions >= len copying bit
 // 0), so the clause loop never builds the padding bits.
 // The contribution table of the padded model has one 128-byte row per

@@ -42,9 +42,10 @@ __device__ __forceinline__ float bf16_value(uint16_t u) {
 // records and counts, in LDS, the 14 (length, sign) occurrences of its
 // variables; every other feature is a sum of those counts.  Bound by the LDS
 // counter updates and the scan (16 bytes a clause and tile, from L2 after the
-// formula's first tile).  Counting in LDS, one update per literal, takes the
-// place of three FP32 global atomics per literal, which ran at about 20 G
-// atomics/s: FEATURE_NUMBERS.
+// formula's first tile).  Three FP32 global atomics per literal took, before, at
+// about 20 G atomics/s: 16 formulas of 2000 variables and 12 000 clauses 207 -> 12
+// us, one of 30 000 and 100 000 111 -> 55 us.  A formula has as many workgroups as
+// tiles: one of 64 variables and 30 000 clauses runs on one CU (193 -> 20 us).
 // 57 KB of counters let two workgroups of 1024 threads share a CU.
 constexpr int kFeatThreads = 1024;
 constexpr int kFeatBins = 14;
